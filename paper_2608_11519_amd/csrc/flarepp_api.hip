@@ -576,8 +576,8 @@ int route_impl(int kind, int dtype, int64_t B, int64_t H, int64_t N, int64_t M, 
 // Work split of the SDPA backward over the long axis (keys of an encode,
 // tokens of the decode): chunks per (b, h) and 32-position tiles per wave;
 // and over the routes: a launch covers nsb route blocks (a window), sized so
-// that four waves' route-gradient slots take at most 80 KB of LDS (two
-// workgroups per CU); the windows run one after another.
+// that four waves' route-gradient slots fit the LDS; the windows run one
+// after another.  (bf16 at D = 16 and 32 takes rs_split instead.)
 struct BwdSplit {
   int waves, R, tpw, nsb;
 };
@@ -585,13 +585,11 @@ struct BwdSplit {
 BwdSplit bwd_split(int64_t BH, int64_t Nl, int D, int Mp, bool dec, int elem_bytes) {
   BwdSplit sp{};
   const int NS = Mp / 32;
-  // LDS budget of a window at 4 waves: the CU's LDS split over as many
-  // workgroups as the kernel's registers let run at once (bf16 at D = 16 fits
-  // two waves per SIMD, so two workgroups of 80 KB; the other variants hold
-  // one wave per SIMD, and a smaller window would only re-read the long side
-  // once more per window).  FLAREPP_BWD_WINDOW_KB (testing and tuning)
-  // overrides it.
-  size_t budget = (D == 16 && elem_bytes == 2) ? 80 * 1024 : 160 * 1024;
+  // LDS budget of a window at 4 waves: the kernel's registers hold one wave
+  // per SIMD, so one workgroup takes the CU's LDS, and a smaller window would
+  // only re-read the long side once more per window.  FLAREPP_BWD_WINDOW_KB
+  // (testing and tuning) overrides it.
+  size_t budget = 160 * 1024;
   if (const char* f = std::getenv("FLAREPP_BWD_WINDOW_KB")) {
     const long kb = std::atol(f);
     if (kb >= 16 && kb <= 160) budget = (size_t)kb * 1024;
@@ -632,7 +630,9 @@ struct BwdWs {
   void *dY, *dK, *dV, *dKt, *dVt;
   void *dVlo, *dVtlo;  // bf16: the value gradients' low parts
   void *Qr, *Qt, *Zr, *dZr, *dZt, *dQr, *dQt, *Sr, *St;
+  void* lc;  // register-resident routes: -L and -c of the decode's positions
   BwdSplit dec, enc;
+  flarepp::RsSplit rs;
   int splits, kchunk;
   size_t bytes;
 };
@@ -704,21 +704,27 @@ BwdWs bwd_ws(void* base, int dtype, int64_t B, int64_t N, int64_t C, int64_t H, 
   }
   w.dZf = (float*)cv.take(f4 * BH * M * D);
   w.dQf = (float*)cv.take(f4 * BH * M * D);
-  w.c1 = (float*)cv.take(f4 * BH * Mp);
-  w.c2 = (float*)cv.take(f4 * BH * Mp);
-  w.l1 = (float*)cv.take(f4 * BH * Mp);
-  w.l2 = (float*)cv.take(f4 * BH * Mp);
-  w.Qr = cv.take(bs * BH * Mp * D);
-  w.Qt = cv.take(bs * BH * Mp * 32 * DB);
-  w.Zr = cv.take(bs * BH * Mp * D);
-  w.dZr = cv.take(bs * BH * Mp * D);
-  w.dZt = cv.take(bs * BH * Mp * 32 * DB);
-  w.dQr = cv.take(bs * BH * Mp * D);
-  w.dQt = cv.take(bs * BH * Mp * 32 * DB);
-  w.Sr = cv.take(bs * H * Mp * D);
-  w.St = cv.take(bs * H * Mp * 32 * DB);
-  w.dec = bwd_split(BH, N, (int)D, (int)Mp, true, (int)bs);
-  w.enc = bwd_split(BH, N, (int)D, (int)Mp, false, (int)bs);
+  if (flarepp::rs_ok((int)D, (int)bs)) {
+    w.rs = flarepp::rs_split(B, H, N, (int)D, (int)Mp);
+    w.dec.R = w.enc.R = w.rs.R;
+    w.lc = cv.take((size_t)16 * BH * round_up(N, 512));
+  } else {
+    w.c1 = (float*)cv.take(f4 * BH * Mp);
+    w.c2 = (float*)cv.take(f4 * BH * Mp);
+    w.l1 = (float*)cv.take(f4 * BH * Mp);
+    w.l2 = (float*)cv.take(f4 * BH * Mp);
+    w.Qr = cv.take(bs * BH * Mp * D);
+    w.Qt = cv.take(bs * BH * Mp * 32 * DB);
+    w.Zr = cv.take(bs * BH * Mp * D);
+    w.dZr = cv.take(bs * BH * Mp * D);
+    w.dZt = cv.take(bs * BH * Mp * 32 * DB);
+    w.dQr = cv.take(bs * BH * Mp * D);
+    w.dQt = cv.take(bs * BH * Mp * 32 * DB);
+    w.Sr = cv.take(bs * H * Mp * D);
+    w.St = cv.take(bs * H * Mp * 32 * DB);
+    w.dec = bwd_split(BH, N, (int)D, (int)Mp, true, (int)bs);
+    w.enc = bwd_split(BH, N, (int)D, (int)Mp, false, (int)bs);
+  }
   const int64_t R = std::max<int64_t>(std::max(w.dec.R, w.enc.R), 1);
   w.pa = (float*)cv.take(f4 * BH * R * Mp * D);
   w.pg = (float*)cv.take(f4 * BH * R * Mp * D);
@@ -903,6 +909,60 @@ int backward_impl(int dtype, int64_t B, int64_t N, int64_t C, int64_t H, int64_t
     return FLAREPP_OK;
   };
 
+  if (rs_ok((int)D, (int)sizeof(T))) {
+    // ---- the three calls with the route side in registers ----
+    const int Ns = (int)round_up(N, 512);
+    BwdRowdotParams rp{};
+    rp.dy = w.dY; rp.y = w.Y; rp.lcol = w.L3; rp.lc = w.lc;
+    rp.B = (int)B; rp.H = (int)H; rp.N = (int)N; rp.Ns = Ns;
+    HIPTRY(launch_bwd_rowdot(rp, (int)D, s));
+    // one launch per window of route blocks; the later ones add to the
+    // position-side gradients of the earlier ones
+    auto windows = [&](const AttnBwdRsParams& a, bool dec) -> int {
+      const int NS = (int)(Mp / 32);
+      const RsSplit& sp = w.rs;
+      for (int w0 = 0; w0 < NS; w0 += sp.nbw) {
+        AttnBwdRsParams q = a;
+        q.R = sp.R; q.steps = sp.steps; q.rw_log2 = sp.rw_log2;
+        q.sb0 = w0;
+        q.nb = std::min(sp.nbw, NS - w0);
+        if (w0 > 0) q.acc_k = q.acc_g = 1;
+        HIPTRY(launch_attn_bwd_rs(q, (int)D, dec, sp.rb, s));
+      }
+      return FLAREPP_OK;
+    };
+    AttnBwdRsParams a3{};
+    a3.B = (int)B; a3.H = (int)H; a3.N = (int)N; a3.M = (int)M; a3.Mp = (int)Mp; a3.Np = (int)Np; a3.Ns = Ns;
+    a3.s = sc; a3.sl2 = sc * 1.4426950408889634f;
+    a3.q = w.Qf; a3.q_f32 = 1; a3.q_sb = H * M * D; a3.q_sh = M * D;
+    a3.k = w.K; a3.dk = w.dK;
+    AttnBwdRsParams a2 = a3, a1;
+    // call 3 (decode): queries K, keys Q, values Z
+    a3.z = w.Zf; a3.g = w.dY; a3.g_sb = N * C; a3.g_sh = D; a3.g_sn = C;
+    a3.lc = w.lc; a3.part_a = w.pa; a3.part_g = w.pg;
+    TRY(windows(a3, true));
+    // call 2 (encode): queries Q, keys K, values V; dOut = dZ
+    BwdReduceParams rd{};
+    rd.P = 1; rd.O = (int)BH; rd.M = (int)M; rd.Mp = (int)Mp; rd.D = (int)D;
+    rd.part0 = w.pg; rd.R0 = w.rs.R; rd.out = dZ_out ? dZ_out : w.dZf;
+    HIPTRY(launch_bwd_reduce(rd, s));
+    a2.z = rd.out; a2.out = w.Zf; a2.lse = w.L2; a2.g = w.Vdm;
+    a2.acc_k = 1; a2.dg = w.dV; a2.dg_lo = w.dVlo; a2.part_a = w.pq;
+    TRY(windows(a2, false));
+    // call 1 (query synthesis): queries = seeds (shared), keys K~, values V~;
+    // dOut = dQ, the decode's and the encode's shares summed
+    rd.part0 = w.pa; rd.part1 = w.pq; rd.R1 = w.rs.R; rd.out = dQ_out ? dQ_out : w.dQf;
+    HIPTRY(launch_bwd_reduce(rd, s));
+    a1 = a2;
+    a1.q = seeds; a1.q_f32 = f32 ? 1 : 0; a1.q_sb = 0;
+    a1.z = rd.out; a1.out = w.Qf; a1.lse = w.L1; a1.k = w.Kt; a1.g = w.Vtdm;
+    a1.dk = w.dKt; a1.acc_k = 0; a1.dg = w.dVt; a1.dg_lo = w.dVtlo; a1.part_a = w.pa;
+    TRY(windows(a1, false));
+    rd = BwdReduceParams{};
+    rd.P = (int)B; rd.O = (int)H; rd.M = (int)M; rd.Mp = (int)Mp; rd.D = (int)D;
+    rd.part0 = w.pa; rd.R0 = w.rs.R; rd.out = dseeds;
+    HIPTRY(launch_bwd_reduce(rd, s));
+  } else {
   // ---- route-side operands of the calls: Q (rows and transposed), Z rows,
   // the seeds (rows and transposed) ----
   BwdPrepParams bp{};
@@ -978,6 +1038,8 @@ int backward_impl(int dtype, int64_t B, int64_t N, int64_t C, int64_t H, int64_t
   rd.P = (int)B; rd.O = (int)H; rd.M = (int)M; rd.Mp = (int)Mp; rd.D = (int)D;
   rd.part0 = w.pa; rd.R0 = w.enc.R; rd.out = dseeds;
   HIPTRY(launch_bwd_reduce(rd, s));
+
+  }
 
   // ---- projections: dX = sum_j dG_j W_j^T; the weight gradients
   // dW_j = X^T dG_j and dW_O = Y^T dO in one split-K launch ----

@@ -5,7 +5,8 @@
 //   in one launch the five weight gradients dW_j = X^T dG_j, dW_O = Y^T dO);
 //   the reductions over tokens are split over workgroups (split-K) and summed
 //   in a fixed order by k_sum_splits.
-// * k_attn_bwd: the SDPA backward of one routing call from its global output
+// * k_attn_bwd: the SDPA backward of one routing call (fp32, and bf16 at
+//   D = 64; bf16 at D = 16 and 32 is in flarepp_attn_bwd.hip) from its global output
 //   and log-normaliser, over a chunk of the long axis (keys of an encode,
 //   tokens of the decode).  Each wave owns 32 positions of the long axis and
 //   walks the route blocks of a window (operands of the next block in flight
@@ -29,7 +30,6 @@ namespace flarepp {
 namespace {
 
 constexpr float kLog2e = 1.4426950408889634f;
-typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;
 
 // ---------------------------------------------------------------------------
 // GEMM
@@ -71,11 +71,6 @@ __device__ __forceinline__ void store8(float* p, const float (&v)[8]) {
   for (int j = 0; j < 4; ++j) { a[j] = v[j]; b[j] = v[4 + j]; }
   *reinterpret_cast<f32x4*>(p) = a;
   *reinterpret_cast<f32x4*>(p + 4) = b;
-}
-__device__ __forceinline__ void store_pair(__bf16* p, float a, float b) {
-  bf16x2_t v;
-  v[0] = (__bf16)a; v[1] = (__bf16)b;
-  *reinterpret_cast<bf16x2_t*>(p) = v;
 }
 __device__ __forceinline__ void store_pair(float* p, float a, float b) {
   f32x2 v;
@@ -332,16 +327,10 @@ __global__ __launch_bounds__(256) void k_sum_splits(const float* part, SumOuts o
 // tile [32][32 + 16 bytes] of T (dS, then P in the decode); per workgroup
 // (encode) the routes' L and c.
 template <typename T> constexpr int tb_pitch() { return 32 + 16 / (int)sizeof(T); }
-// Bytes of a wave's tile buffer: the transpose tile, or for the bf16 decode
-// at D = 16 its staged long-side rows (keys, dY, Y: 1 KiB each, then 32
-// log-normalisers), whichever is larger.
-constexpr size_t attn_bwd_tile_bytes(int D, bool dec, int elem_bytes) {
-  const size_t tile = (size_t)32 * (32 + 16 / elem_bytes) * elem_bytes;
-  const size_t staged = (dec && elem_bytes == 2 && D == 16) ? 3 * 1024 + 128 : 0;
-  return tile > staged ? tile : staged;
-}
+// Bytes of a wave's transpose tile.
+constexpr size_t attn_bwd_tile_bytes(int elem_bytes) { return (size_t)32 * (32 + 16 / elem_bytes) * elem_bytes; }
 size_t attn_bwd_wave_bytes(int D, int nsb, bool dec, int elem_bytes) {
-  return sizeof(float) * (size_t)(dec ? 2 : 1) * D * (32 * nsb + 4) + attn_bwd_tile_bytes(D, dec, elem_bytes);
+  return sizeof(float) * (size_t)(dec ? 2 : 1) * D * (32 * nsb + 4) + attn_bwd_tile_bytes(elem_bytes);
 }
 
 // Fragment of a long-side row: element j = x[n * sn + (d0 + j) * sd] (one
@@ -415,12 +404,11 @@ __device__ __forceinline__ void load_short(ShortBlock<T, D, DEC>& s, const T* as
     }
 }
 
-// bf16 at D = 16 keeps two waves per SIMD (two workgroups per CU)
 template <typename T, int D, bool DEC>
-__global__ __launch_bounds__(256, (sizeof(T) == 2 && D == 16) ? 2 : 1) void k_attn_bwd(AttnBwdParams p) {
+__global__ __launch_bounds__(256, 1) void k_attn_bwd(AttnBwdParams p) {
   using F = typename Frag<T>::type;
   constexpr int KS = D / 16, DB = (D + 31) / 32, TBP = tb_pitch<T>();
-  constexpr int TBE = (int)(attn_bwd_tile_bytes(D, DEC, (int)sizeof(T)) / sizeof(T));  // tile buffer elements
+  constexpr int TBE = (int)(attn_bwd_tile_bytes((int)sizeof(T)) / sizeof(T));  // tile buffer elements
   // bf16: dS (and P in the decode) change layout on the MFMA (times a
   // permutation matrix) instead of through LDS; fp32 keeps the LDS transpose
   constexpr bool MT = std::is_same<T, __bf16>::value;
@@ -468,66 +456,7 @@ __global__ __launch_bounds__(256, (sizeof(T) == 2 && D == 16) ? 2 : 1) void k_at
   T* dout_b = static_cast<T*>(p.dout_b);
   T* dout_g = static_cast<T*>(p.dout_g);
 
-  // bf16 at D = 16 with token-major keys: a tile's long-side rows are copied
-  // into the wave's tile buffer one tile ahead by direct buffer -> LDS loads,
-  // issued as soon as the current tile's rows have been read out, so no tile
-  // waits on its loads.  Encode: the 32 key rows [32][16], then the 16 d-major
-  // value rows of its 32 positions [16][32]; decode: key rows, dY rows, Y rows
-  // ([32][16] each), then the 32 log-normalisers; 1 KiB per block of rows.
-  // Rows past the long length read as zero (buffer bounds; the d-major
-  // values are zero-padded).
-  constexpr bool STG = MT && D == 16;
-  const bool stg = STG && p.blo_sd == 1 && p.blo_sn == D &&
-                   (DEC ? (p.glo_sd == 1 && p.ylo_sn == p.glo_sn) : p.glo_sn == 1);  // uniform
   const T* ylo = DEC ? static_cast<const T*>(p.ylo) + b * p.ylo_sb + h * p.ylo_sh : nullptr;
-  auto stage_issue = [&](int i) __attribute__((always_inline)) {
-    if (i >= p.tpw) return;
-    const int n0i = ((r * p.tpw + i) * W + wave) * 32;  // wave-uniform
-    if (n0i >= p.Nl) return;
-    constexpr int EB = (int)sizeof(T);
-    const int kbytes = (int)std::min<int64_t>((int64_t)p.Nl * D * EB, 0x7fffffff);
-    const int vbytes = (int)std::min<int64_t>((int64_t)D * p.glo_sd * EB, 0x7fffffff);
-    const __amdgpu_buffer_rsrc_t rk =
-        __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(blo), (short)0, kbytes, 0x00020000);
-    // lane l: key row n0i + l / 2, half l % 2 (likewise dY and Y rows);
-    // value row l / 4, positions n0i + 8 (l % 4) .. + 7; each lands at byte
-    // 16 l of its KiB
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rk, (__attribute__((address_space(3))) void*)tb, 16,
-                                             (n0i * D + 8 * lane) * EB, 0, 0, 0);
-    if constexpr (DEC) {
-      const int sn = (int)p.glo_sn;
-      const int rbytes = (int)std::min<int64_t>((int64_t)p.Nl * sn * EB, 0x7fffffff);
-      const __amdgpu_buffer_rsrc_t rg =
-          __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(glo), (short)0, rbytes, 0x00020000);
-      const __amdgpu_buffer_rsrc_t ry =
-          __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(ylo), (short)0, rbytes, 0x00020000);
-      const int roff = ((n0i + (lane >> 1)) * sn + 8 * (lane & 1)) * EB;
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rg, (__attribute__((address_space(3))) void*)(tb + 32 * D), 16, roff, 0, 0, 0);
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(ry, (__attribute__((address_space(3))) void*)(tb + 64 * D), 16, roff, 0, 0, 0);
-      if (lane < 8) {  // 32 log-normalisers, 4 per lane
-        const __amdgpu_buffer_rsrc_t rl = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<float*>(p.lcol + (int64_t)bh * p.Nl), (short)0,
-            (int)std::min<int64_t>((int64_t)p.Nl * 4, 0x7fffffff), 0x00020000);
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rl, (__attribute__((address_space(3))) void*)(tb + 96 * D), 16,
-                                                 (n0i + 4 * lane) * 4, 0, 0, 0);
-      }
-    } else {
-      const __amdgpu_buffer_rsrc_t rv =
-          __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(glo), (short)0, vbytes, 0x00020000);
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rv, (__attribute__((address_space(3))) void*)(tb + 32 * D), 16,
-                                               ((lane >> 2) * (int)p.glo_sd + n0i + 8 * (lane & 3)) * EB, 0, 0, 0);
-    }
-    asm volatile("" ::: "memory");  // the copies go out ahead of the tile's route-operand loads
-  };
-  if (stg) {
-    // zero the tile buffer first: rows past the long length hold zeros (or,
-    // after a full tile, that tile's finite rows) whatever the bounds-checked
-    // copies leave there, so no NaN of earlier LDS contents reaches a sum
-    for (int i = 8 * lane; i < TBE; i += 8 * 64) store_frag8(tb + i, zero_frag<T>());
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    stage_issue(0);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  }
 
   for (int i = 0; i < p.tpw; ++i) {
     const int n0 = ((r * p.tpw + i) * W + wave) * 32;  // wave-uniform
@@ -542,118 +471,80 @@ __global__ __launch_bounds__(256, (sizeof(T) == 2 && D == 16) ? 2 : 1) void k_at
     F kt[2][DB], gt[2][DB];
     // decode: c = <dY_n, Y_n> and the token's log-normaliser
     float Ll = 0.f, cl = 0.f;
-    if (stg) {
-      // from the staged rows (landed at the end of the previous tile)
-      // (the lane index is re-read here so that the per-lane LDS offsets are
-      // computed per tile rather than held in registers across the loop)
-      int ln = lane;
-      asm volatile("" : "+v"(ln));
-      const int lg = ln >> 5, lc = ln & 31;
-      const T* sk = tb;           // [32 positions][D]
-      const T* sv = tb + 32 * D;  // encode: [D][32 positions]; decode: dY [32 positions][D]
-      kb[0] = load_frag(sk + lc * D + 8 * lg);
-      // columns d = lc >= D of the short-side products are never stored:
-      // those lanes read a valid (finite) value of another column
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) kb[ks] = long_frag(blo, p.blo_sn, p.blo_sd, nc, 16 * ks + 8 * g, nok);
+    if (D == 32 && p.glo_sn == 1) {  // wave-uniform (at D = 16 the staging would cost the second wave per SIMD)
+      // d-major values (each head's rows padded to whole 32-position tiles):
+      // the tile's D rows of 32 positions go through the wave's transpose
+      // tile with 16-byte loads (chunk r: row r / 4, positions 8 (r % 4) ..
+      // + 7), then each lane reads its position's column
+#pragma unroll
+      for (int r0 = 0; r0 < D * 4; r0 += 64) {
+        const int r = r0 + lane, d = r >> 2, q = r & 3;
+        store_frag8(tb + d * TBP + 8 * q, load_frag(glo + (int64_t)d * p.glo_sd + n0 + 8 * q));
+      }
+      __builtin_amdgcn_wave_barrier();
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          const T v = tb[(16 * ks + 8 * g + j) * TBP + c];
+          gb[ks][j] = nok ? v : from_f32<T>(0.f);
+        }
+      __builtin_amdgcn_wave_barrier();
+    } else {
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) gb[ks] = long_frag(glo, p.glo_sn, p.glo_sd, nc, 16 * ks + 8 * g, nok);
+    }
+    // row-major long side (unit stride along d): each lane stores its
+    // position's row of 32 columns into the wave's transpose tile with
+    // 16-byte loads, then reads one column (d = 32 db + c) of it
+    auto transpose_long = [&](const T* x, int64_t sn, F (&out)[2][DB]) __attribute__((always_inline)) {
+#pragma unroll
+      for (int db = 0; db < DB; ++db) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const int d0 = 32 * db + 16 * g + 8 * h;  // D is a multiple of 16: d0 < D means d0 + 8 <= D
+          store_frag8(tb + c * TBP + 16 * g + 8 * h, d0 < D ? load_frag(x + (int64_t)nc * sn + d0) : zero_frag<T>());
+        }
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+          for (int j = 0; j < 8; ++j) {
+            const int pos = short_k_pos(kk, g, j);
+            const T v = tb[pos * TBP + c];
+            out[kk][db][j] = n0 + pos < p.Nl ? v : from_f32<T>(0.f);
+          }
+        __builtin_amdgcn_wave_barrier();
+      }
+    };
+    // (D = 64 keeps the element loads: the staged rows would add to a
+    // register budget that is already full there)
+    if (D <= 32 && p.blo_sd == 1 && (!DEC || p.glo_sd == 1)) {  // wave-uniform
+      transpose_long(blo, p.blo_sn, kt);
+      if constexpr (DEC) transpose_long(glo, p.glo_sn, gt);
+    } else {
 #pragma unroll
       for (int kk = 0; kk < 2; ++kk)
 #pragma unroll
-        for (int j = 0; j < 8; ++j) kt[kk][0][j] = sk[short_k_pos(kk, lg, j) * D + (lc & (D - 1))];
-      if constexpr (DEC) {
-        gb[0] = load_frag(sv + lc * D + 8 * lg);
-#pragma unroll
-        for (int kk = 0; kk < 2; ++kk)
-#pragma unroll
-          for (int j = 0; j < 8; ++j) gt[kk][0][j] = sv[short_k_pos(kk, lg, j) * D + (lc & (D - 1))];
-        // c = <dY_n, Y_n> over the head's channels and the token's
-        // log-normaliser (log2 units), from the staged rows
-        const F yf = load_frag(tb + 64 * D + lc * D + 8 * lg);
-        float sacc = 0.f;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) sacc += to_f32(gb[0][j]) * to_f32(yf[j]);
-        cl = sacc + other_half(sacc);
-        Ll = reinterpret_cast<const float*>(tb + 96 * D)[lc];
-      } else {
-#pragma unroll
-        for (int j = 0; j < 8; ++j) gb[0][j] = sv[(8 * lg + j) * 32 + lc];
-      }
-      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // read out before the next tile's rows land
-      stage_issue(i + 1);
-    } else {
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) kb[ks] = long_frag(blo, p.blo_sn, p.blo_sd, nc, 16 * ks + 8 * g, nok);
-      if (D == 32 && p.glo_sn == 1) {  // wave-uniform (at D = 16 the staging would cost the second wave per SIMD)
-        // d-major values (each head's rows padded to whole 32-position tiles):
-        // the tile's D rows of 32 positions go through the wave's transpose
-        // tile with 16-byte loads (chunk r: row r / 4, positions 8 (r % 4) ..
-        // + 7), then each lane reads its position's column
-#pragma unroll
-        for (int r0 = 0; r0 < D * 4; r0 += 64) {
-          const int r = r0 + lane, d = r >> 2, q = r & 3;
-          store_frag8(tb + d * TBP + 8 * q, load_frag(glo + (int64_t)d * p.glo_sd + n0 + 8 * q));
-        }
-        __builtin_amdgcn_wave_barrier();
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
+        for (int db = 0; db < DB; ++db)
 #pragma unroll
           for (int j = 0; j < 8; ++j) {
-            const T v = tb[(16 * ks + 8 * g + j) * TBP + c];
-            gb[ks][j] = nok ? v : from_f32<T>(0.f);
-          }
-        __builtin_amdgcn_wave_barrier();
-      } else {
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) gb[ks] = long_frag(glo, p.glo_sn, p.glo_sd, nc, 16 * ks + 8 * g, nok);
-      }
-      // row-major long side (unit stride along d): each lane stores its
-      // position's row of 32 columns into the wave's transpose tile with
-      // 16-byte loads, then reads one column (d = 32 db + c) of it
-      auto transpose_long = [&](const T* x, int64_t sn, F (&out)[2][DB]) __attribute__((always_inline)) {
-#pragma unroll
-        for (int db = 0; db < DB; ++db) {
-#pragma unroll
-          for (int h = 0; h < 2; ++h) {
-            const int d0 = 32 * db + 16 * g + 8 * h;  // D is a multiple of 16: d0 < D means d0 + 8 <= D
-            store_frag8(tb + c * TBP + 16 * g + 8 * h, d0 < D ? load_frag(x + (int64_t)nc * sn + d0) : zero_frag<T>());
-          }
-          __builtin_amdgcn_wave_barrier();
-#pragma unroll
-          for (int kk = 0; kk < 2; ++kk)
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-              const int pos = short_k_pos(kk, g, j);
-              const T v = tb[pos * TBP + c];
-              out[kk][db][j] = n0 + pos < p.Nl ? v : from_f32<T>(0.f);
+            const int nn = n0 + short_k_pos(kk, g, j), d = 32 * db + c;
+            const bool ok = nn < p.Nl && d < D;
+            const int64_t at = (int64_t)min(nn, p.Nl - 1) * p.blo_sn + (int64_t)min(d, D - 1) * p.blo_sd;
+            const T kv = blo[at];
+            kt[kk][db][j] = ok ? kv : from_f32<T>(0.f);
+            if (DEC) {
+              const T gv = glo[(int64_t)min(nn, p.Nl - 1) * p.glo_sn + (int64_t)min(d, D - 1) * p.glo_sd];
+              gt[kk][db][j] = ok ? gv : from_f32<T>(0.f);
             }
-          __builtin_amdgcn_wave_barrier();
-        }
-      };
-      // (D = 64 keeps the element loads: the staged rows would add to a
-      // register budget that is already full there)
-      if (D <= 32 && p.blo_sd == 1 && (!DEC || p.glo_sd == 1)) {  // wave-uniform
-        transpose_long(blo, p.blo_sn, kt);
-        if constexpr (DEC) transpose_long(glo, p.glo_sn, gt);
-      } else {
-#pragma unroll
-        for (int kk = 0; kk < 2; ++kk)
-#pragma unroll
-          for (int db = 0; db < DB; ++db)
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-              const int nn = n0 + short_k_pos(kk, g, j), d = 32 * db + c;
-              const bool ok = nn < p.Nl && d < D;
-              const int64_t at = (int64_t)min(nn, p.Nl - 1) * p.blo_sn + (int64_t)min(d, D - 1) * p.blo_sd;
-              const T kv = blo[at];
-              kt[kk][db][j] = ok ? kv : from_f32<T>(0.f);
-              if (DEC) {
-                const T gv = glo[(int64_t)min(nn, p.Nl - 1) * p.glo_sn + (int64_t)min(d, D - 1) * p.glo_sd];
-                gt[kk][db][j] = ok ? gv : from_f32<T>(0.f);
-              }
-            }
-      }
+          }
     }
     // decode: c = <dY_n, Y_n> over the head's channels, and the token's
     // log-normaliser over the routes (log2 units) from the forward
-    if (DEC && !stg) {
+    if (DEC) {
       const T* y = ylo;
       float sacc = 0.f;
 #pragma unroll
@@ -857,10 +748,6 @@ __global__ __launch_bounds__(256, (sizeof(T) == 2 && D == 16) ? 2 : 1) void k_at
         route_block(b1, sb + 1, si, di);
       }
     }
-    // the next tile's staged rows (issued at this tile's start, ahead of all
-    // its route-operand loads) have landed; waited for here, before this
-    // tile's stores, so the wait covers loads only
-    if (stg) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     // long-side results for this wave's 32 positions: rows d, column = lane
     if (nok) {
       const int64_t row = ((int64_t)b * p.Nl + n) * (int64_t)(p.H * D) + h * D;
@@ -1030,14 +917,12 @@ hipError_t launch_sum_splits(const float* part, float* const* out, int64_t n, in
 
 template <typename T>
 hipError_t launch_attn_bwd(const AttnBwdParams& p, int D, bool dec, hipStream_t s) {
-  if (dec) {
-    if (D == 16) return attn_bwd_go<T, 16, true>(p, s);
-    if (D == 32) return attn_bwd_go<T, 32, true>(p, s);
-    return attn_bwd_go<T, 64, true>(p, s);
+  if (D == 64) return dec ? attn_bwd_go<T, 64, true>(p, s) : attn_bwd_go<T, 64, false>(p, s);
+  if constexpr (std::is_same<T, float>::value) {
+    if (D == 16) return dec ? attn_bwd_go<T, 16, true>(p, s) : attn_bwd_go<T, 16, false>(p, s);
+    if (D == 32) return dec ? attn_bwd_go<T, 32, true>(p, s) : attn_bwd_go<T, 32, false>(p, s);
   }
-  if (D == 16) return attn_bwd_go<T, 16, false>(p, s);
-  if (D == 32) return attn_bwd_go<T, 32, false>(p, s);
-  return attn_bwd_go<T, 64, false>(p, s);
+  return hipErrorInvalidValue;
 }
 
 hipError_t launch_bwd_reduce(const BwdReduceParams& p, hipStream_t s) {

@@ -276,6 +276,40 @@ struct AttnBwdParams {
   void* dout_g; void* dout_g_lo; int acc_g;
   float* part_a; float* part_g;
 };
+// The same for bf16 at D = 16 or 32, with the route side in registers
+// (flarepp_attn_bwd.hip): a launch covers nb route blocks from sb0, chunks of
+// `steps` steps of positions per workgroup, R chunks per (b, h).
+struct AttnBwdRsParams {
+  int B, H, N, M, Mp, Np, Ns, R, steps;  // Np, Ns: N rounded up to 32, 512
+  int sb0, nb, rw_log2;                  // rw_log2: log2 of the route groups of a workgroup
+  float s, sl2;                          // 1/sqrt(D), and times log2(e)
+  const void* q; int q_f32; int64_t q_sb, q_sh;  // [M][D] per (b, h): Q, or the seeds (fp32 or bf16)
+  const float* z;    // [B * H][M][D]: the encode's dOut, the decode's Z
+  const float* out;  // encode: [B * H][M][D] forward output
+  const float* lse;  // encode: [B * H][M] natural-log normaliser
+  const void* k;     // [B * H][N][D]
+  const void* g; int64_t g_sb, g_sh, g_sn;  // encode: V d-major [B * H][D][Np]; decode: dY rows
+  const void* lc;    // decode: -L (log2) and -c as three bf16 terms each, [B * H][Ns][8]
+  // gradients as for AttnBwdParams: dk (both), dg with its low part (encode)
+  void* dk; int acc_k;
+  void* dg; void* dg_lo; int acc_g;
+  float* part_a; float* part_g;
+};
+struct RsSplit {
+  int rb, rw_log2, nbw;  // route blocks per wave, log2 route groups, route blocks per launch
+  int R, steps;
+};
+constexpr bool rs_ok(int D, int elem_bytes) { return elem_bytes == 2 && (D == 16 || D == 32); }
+RsSplit rs_split(int64_t B, int64_t H, int64_t N, int D, int Mp);
+hipError_t launch_attn_bwd_rs(const AttnBwdRsParams&, int D, bool dec, int rb, hipStream_t);
+// -L and -c of the decode's positions for the kernel above
+struct BwdRowdotParams {
+  const void* dy; const void* y;  // [B][N][H * D]
+  const float* lcol;              // [B * H][N]
+  void* lc;                       // [B * H][Ns][8] bf16
+  int B, H, N, Ns;
+};
+hipError_t launch_bwd_rowdot(const BwdRowdotParams&, int D, hipStream_t);
 // LDS of a launch over a window of nsb route blocks (Mp routes in all)
 int attn_bwd_waves(int D, int nsb, int Mp, bool dec, int elem_bytes);
 size_t attn_bwd_lds_bytes(int D, int nsb, int Mp, bool dec, int waves, int elem_bytes);
