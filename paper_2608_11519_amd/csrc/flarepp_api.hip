@@ -1455,19 +1455,17 @@ int flarepp_block_backward(int dtype, int64_t B, int64_t N, int64_t C, int64_t H
   flarepp::LayerNormBwdParams lb{};
   lb.x = X; lb.gamma = gamma; lb.mean = w.mean; lb.rstd = w.rstd; lb.dxn = w.dxn; lb.dO = dO; lb.dx = dX;
   lb.part = w.part; lb.T = B * N; lb.C = (int)C; lb.nchunks = w.nchunks; lb.chunk = w.chunk;
-  float* dgb[2] = {dgamma, dbeta};
   if (dtype == FLAREPP_F32) {
     HIPTRY(flarepp::launch_layernorm<float>(lp, s));
     TRY(backward_impl<float>(dtype, B, N, C, H, M, w.xn, Wk, Wv, Wkt, Wvt, Wo, seeds, dO, w.dxn, dWk, dWv, dWkt,
                              dWvt, dWo, dseeds, nullptr, nullptr, w.ws, w.ws_bytes, s));
-    HIPTRY(flarepp::launch_layernorm_bwd<float>(lb, s));
+    HIPTRY(flarepp::launch_layernorm_bwd<float>(lb, dgamma, dbeta, s));
   } else {
     HIPTRY(flarepp::launch_layernorm<__bf16>(lp, s));
     TRY(backward_impl<__bf16>(dtype, B, N, C, H, M, w.xn, Wk, Wv, Wkt, Wvt, Wo, seeds, dO, w.dxn, dWk, dWv, dWkt,
                               dWvt, dWo, dseeds, nullptr, nullptr, w.ws, w.ws_bytes, s));
-    HIPTRY(flarepp::launch_layernorm_bwd<__bf16>(lb, s));
+    HIPTRY(flarepp::launch_layernorm_bwd<__bf16>(lb, dgamma, dbeta, s));
   }
-  HIPTRY(flarepp::launch_sum_splits(w.part, dgb, C, w.nchunks, 2, s));
   return ok();
 }
 

@@ -350,7 +350,8 @@ template <typename T> hipError_t launch_bwd_prep(const BwdPrepParams&, hipStream
 int64_t bwd_prep_items(const BwdPrepParams&, int job);
 
 template <typename T> hipError_t launch_layernorm(const LayerNormParams&, hipStream_t);
-template <typename T> hipError_t launch_layernorm_bwd(const LayerNormBwdParams&, hipStream_t);
+// with dgamma and dbeta [C], the sums of the chunks' partials
+template <typename T> hipError_t launch_layernorm_bwd(const LayerNormBwdParams&, float* dgamma, float* dbeta, hipStream_t);
 template <typename T> hipError_t launch_weight_frags(const WeightFragParams&, hipStream_t);
 template <typename Ts, typename T> hipError_t launch_route_prep(const RoutePrepParams&, hipStream_t);
 template <typename T> hipError_t launch_dmajor(const DmajorParams&, hipStream_t);

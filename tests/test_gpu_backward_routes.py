@@ -75,3 +75,25 @@ def test_large_scores_of_one_sign(C, H, sign):
     got = _grads(w, d, inp.make_tensor((1, 75, C), 25, "bf16"))
     for k in GRADS:
         assert np.isfinite(got[k]).all(), k
+
+
+@pytest.mark.parametrize("B,N,C,H", [(1, 1, 32, 2), (1, 70, 64, 4), (2, 1061, 128, 8), (1, 130, 512, 16), (1, 37, 1024, 16)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_block_layer_norm_gradients(B, N, C, H, dtype):
+    # 4 to 64 lanes per token (C = 1024: two runs per lane), token counts
+    # around a workgroup's chunk (1061 x 2 tokens: two per chunk, a short last
+    # one)
+    w = inp.Workload("ln-edge", B, N, C, H, 16, dtype, "normal")
+    d = inp.make_inputs(w, 31)
+    t = upload(d, w)
+    gamma = inp.make_tensor((C,), 32, dtype) * 0.25 + 1
+    gamma = inp.round_to_bf16(gamma) if dtype == "bf16" else gamma.astype(np.float32)
+    beta = inp.make_tensor((C,), 33, dtype)
+    dO = inp.make_tensor((B, N, C), 34, dtype)
+    up = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to("cuda", t["X"].dtype)  # noqa: E731
+    g = fp.flarepp_block_backward(t["X"], up(gamma), up(beta), t["Wk"], t["Wv"], t["Wkt"], t["Wvt"], t["Wo"],
+                                  t["seeds"], up(dO), H=H, eps=1e-5)
+    torch.cuda.synchronize()
+    ref = orc.block_backward(d["X"], gamma, beta, 1e-5, d["Wk"], d["Wv"], d["Wkt"], d["Wvt"], d["Wo"], d["seeds"], H, dO)
+    for k in ("dX", "dgamma", "dbeta"):
+        assert_close(k, g[k].cpu().numpy(), ref[k], TOL[dtype], inp.describe(w))
