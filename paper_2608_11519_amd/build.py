@@ -15,7 +15,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libflarepp.so")
 SOURCES = ["flarepp_kernels.hip", "flarepp_fused.hip", "flarepp_backward.hip",
-           "flarepp_attn_bwd.hip", "flarepp_api.hip"]
+           "flarepp_attn_bwd.hip", "flarepp_grad_gemm.hip", "flarepp_api.hip"]
 ARCH = "gfx950"
 
 

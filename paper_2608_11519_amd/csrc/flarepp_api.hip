@@ -621,7 +621,8 @@ int gemm_splits(int64_t T, int64_t C, int* kchunk) {
 }
 
 struct BwdWs {
-  void *wf[4], *seeds_op, *K, *Kt, *Vdm, *Vtdm, *Y, *q_op, *z_op;
+  void *wf[5], *wft[5];  // fragments of the five weights (W_O's for a training forward), and of their transposes
+  void *seeds_op, *K, *Kt, *Vdm, *Vtdm, *Y, *q_op, *z_op;
   void *fwf[2], *fq_op;  // fused encodes: W_K (key order), W_V fragments; Q(X) in q fragment order
   void *fwo, *fz_op;     // fused decode: W_O merge fragments, Z in z fragment order
   float* fqnorm2;        // fused decode: route-norm bounds of Q(X)
@@ -634,6 +635,7 @@ struct BwdWs {
   BwdSplit dec, enc;
   flarepp::RsSplit rs;
   int splits, kchunk;
+  int wg_prob; int64_t wg_chunk;  // k_wgrad's problems and tokens per chunk
   size_t bytes;
 };
 
@@ -665,7 +667,9 @@ BwdWs bwd_ws(void* base, int dtype, int64_t B, int64_t N, int64_t C, int64_t H, 
   const EncPlan e = encode_plan(B, H, N, Mp, D);
   Carver cv(base);
   BwdWs w{};
-  for (int i = 0; i < 4; ++i) w.wf[i] = cv.take(bs * C * C);
+  const bool gg = flarepp::grad_gemm_ok((int)C, (int)bs), rs = flarepp::rs_ok((int)D, (int)bs);
+  for (int i = 0; i < (dtype == FLAREPP_BF16 ? 5 : 4); ++i) w.wf[i] = cv.take(bs * C * C);
+  for (int i = 0; i < 5; ++i) w.wft[i] = (i < 4 ? gg : rs) ? cv.take(bs * C * C) : nullptr;
   w.seeds_op = cv.take(bs * H * Mp * D);
   w.K = cv.take(bs * BH * N * D);
   w.Kt = cv.take(bs * BH * N * D);
@@ -704,10 +708,10 @@ BwdWs bwd_ws(void* base, int dtype, int64_t B, int64_t N, int64_t C, int64_t H, 
   }
   w.dZf = (float*)cv.take(f4 * BH * M * D);
   w.dQf = (float*)cv.take(f4 * BH * M * D);
-  if (flarepp::rs_ok((int)D, (int)bs)) {
+  if (rs) {
     w.rs = flarepp::rs_split(B, H, N, (int)D, (int)Mp);
     w.dec.R = w.enc.R = w.rs.R;
-    w.lc = cv.take((size_t)16 * BH * round_up(N, 512));
+    w.lc = cv.take((size_t)16 * BH * N);
   } else {
     w.c1 = (float*)cv.take(f4 * BH * Mp);
     w.c2 = (float*)cv.take(f4 * BH * Mp);
@@ -729,8 +733,14 @@ BwdWs bwd_ws(void* base, int dtype, int64_t B, int64_t N, int64_t C, int64_t H, 
   w.pa = (float*)cv.take(f4 * BH * R * Mp * D);
   w.pg = (float*)cv.take(f4 * BH * R * Mp * D);
   w.pq = (float*)cv.take(f4 * BH * R * Mp * D);
-  w.splits = gemm_splits(T, C, &w.kchunk);
-  w.gpart = (float*)cv.take(f4 * 5 * w.splits * C * C);
+  if (gg) {
+    w.wg_prob = bwd_lo_parts(dtype) ? 7 : 5;
+    w.splits = flarepp::wgrad_chunks(T, (int)C, w.wg_prob, &w.wg_chunk);
+    w.gpart = (float*)cv.take(f4 * w.wg_prob * w.splits * C * C);
+  } else {
+    w.splits = gemm_splits(T, C, &w.kchunk);
+    w.gpart = (float*)cv.take(f4 * 5 * w.splits * C * C);
+  }
   w.bytes = cv.off;
   return w;
 }
@@ -775,8 +785,14 @@ int backward_impl(int dtype, int64_t B, int64_t N, int64_t C, int64_t H, int64_t
   if (mode != kBwdReverse) {
   WeightFragParams wp{};
   wp.C = (int)C;
-  for (int i = 0; i < 4; ++i) { wp.w[i] = w_in[i]; wp.out[i] = w.wf[i]; }
-  wp.nw = 4;
+  auto frags = [&](const void* wt, void* out, int trans) {
+    wp.w[wp.nw] = wt; wp.out[wp.nw] = out; wp.trans[wp.nw] = trans; ++wp.nw;
+  };
+  for (int i = 0; i < 4; ++i) frags(w_in[i], w.wf[i], 0);
+  if (w.wf[4] && mode == kBwdForward) frags(Wo, w.wf[4], 0);
+  // for the reverse pass: dX = sum_j dG_j W_j^T, dY = dO W_O^T
+  for (int i = 0; i < 5; ++i)
+    if (w.wft[i]) frags(i < 4 ? w_in[i] : Wo, w.wft[i], 1);
   HIPTRY(launch_weight_frags<T>(wp, s));
   ProjParams pp{};
   pp.x = X; pp.B = (int)B; pp.N = (int)N; pp.Np = (int)Np; pp.C = (int)C; pp.H = (int)H; pp.D = (int)D;
@@ -787,33 +803,17 @@ int backward_impl(int dtype, int64_t B, int64_t N, int64_t C, int64_t H, int64_t
   pp.wf[3] = w.wf[3]; pp.out[3] = w.Vtdm; pp.layout[3] = kHeadsDMajor;
   HIPTRY(launch_project<T>(pp, s));
   const MixerPlan pl = mixer_plan(dtype, B, N, C, H, M);
-  // call 3 on the unfused decode (route operands as rows of Q(X) scaled and
-  // Z d-major), which writes Y and the per-token log-normaliser
-  auto unfused_call3 = [&]() -> int {
-    RouteParams r3 = decode_params(B, H, N, M, D);
-    r3.ka = w.q_op; r3.ka_sb = rtBS; r3.ka_sh = rtHS; r3.ka_rows = (int)Mp;
-    r3.va = w.z_op; r3.va_sb = H * D * Mp; r3.va_sh = D * Mp; r3.va_ld = (int)Mp;
-    r3.qs = w.K; r3.qs_sb = tokBS; r3.qs_sh = tokHS; r3.qs_rows = (int)N;
-    r3.y = w.Y; r3.y_sb = N * C; r3.y_row = C; r3.lse2 = w.L3;
-    HIPTRY(launch_route<T>(r3, (int)D, true, s));
-    return FLAREPP_OK;
-  };
   if (bwd_fused_encodes(dtype, pl)) {
-    // calls 1 and 2 on the fused encodes, as in the forward.  Call 3 on the
-    // fused decode where it has the per-group stages (C <= 128; the first
-    // combine then also writes W_O's merge fragments): it writes Y and the
-    // per-token log-normaliser for the reverse pass, and O (the training
-    // forward's output; otherwise into dY's buffer, which the merge gradient
-    // overwrites).  At C = 256 the unfused decode is the faster one here (no
-    // projection or merge to repeat): the combines write its route operands.
+    // the three calls on the fused kernels, as in the forward; the decode
+    // writes Y and the per-token log-normaliser for the reverse pass, and O
+    // for the training forward alone (without it the merge is skipped)
     const int dkind = decode_kind_for((int)C, (int)D, (int)Mp, (int)dtype_bytes(dtype));
-    const bool fdec = dkind != kDecodeStaged;
     PrepFusedParams fp{};
     fp.C = (int)C;
     fp.w[0] = Wk; fp.wf[0] = w.fwf[0]; fp.mode[0] = kFragKeyPerm;
     fp.w[1] = Wv; fp.wf[1] = w.fwf[1]; fp.mode[1] = kFragPlain;
     fp.w[2] = Wo; fp.wf[2] = w.fwo; fp.mode[2] = dkind == kDecodeStaged ? kFragMerge : kFragMergeHg;
-    fp.nw = fdec ? 3 : 2;
+    fp.nw = 3;
     fp.seeds = seeds; fp.H = (int)H; fp.M = (int)M; fp.Mp = (int)Mp; fp.D = (int)D; fp.qscale = qscale;
     EncFusedParams ep{};
     ep.x = X; ep.wk_raw = Wkt; ep.wv_raw = Wvt; ep.seeds_raw = seeds;
@@ -826,31 +826,27 @@ int backward_impl(int dtype, int64_t B, int64_t N, int64_t C, int64_t H, int64_t
     cp.part_ml = w.part_ml; cp.part_acc = w.part_acc; cp.BH = BH; cp.R = pl.nchunks;
     cp.M = (int)M; cp.Mp = (int)Mp; cp.D = (int)D; cp.qscale = qscale; cp.frag = 1;
     cp.out32 = w.Qf; cp.lse = w.L1; cp.q_op = w.fq_op;
-    cp.qnorm2 = fdec ? w.fqnorm2 : nullptr; cp.q_rows = fdec ? nullptr : w.q_op;
+    cp.qnorm2 = w.fqnorm2;
     cp.prep = fp; cp.prep_n = prep_fused_items(fp);
     HIPTRY(launch_combine_par<T>(cp, s));
     ep.wk_raw = ep.wv_raw = ep.seeds_raw = nullptr;
     ep.wkf = w.fwf[0]; ep.wvf = w.fwf[1]; ep.q_op = w.fq_op; ep.q_sb = H * Mp * D;
     HIPTRY(launch_encode_fused<T>(ep, (int)D, pl.waves, s));
-    cp.out32 = w.Zf; cp.lse = w.L2; cp.q_op = nullptr; cp.qnorm2 = nullptr; cp.q_rows = nullptr;
-    cp.z_op = fdec ? w.fz_op : nullptr; cp.z_rows = fdec ? nullptr : w.z_op;
+    cp.out32 = w.Zf; cp.lse = w.L2; cp.q_op = nullptr; cp.qnorm2 = nullptr;
+    cp.z_op = w.fz_op;
     cp.prep_n = 0;
     HIPTRY(launch_combine_par<T>(cp, s));
-    if (!fdec) {
-      TRY(unfused_call3());
-    } else {
     DecFusedParams dp{};
     dp.x = X; dp.wkf = w.fwf[0]; dp.wof = w.fwo; dp.q_op = w.fq_op; dp.z_op = w.fz_op; dp.qnorm2 = w.fqnorm2;
     dp.B = (int)B; dp.N = (int)N; dp.C = (int)C; dp.H = (int)H; dp.M = (int)M; dp.Mp = (int)Mp;
     dp.fast_lim = fast_limit(); dp.y = w.Y; dp.lse2 = w.L3;
-    dp.o = mode == kBwdForward ? O : w.dY; dp.res = nullptr;
+    dp.o = mode == kBwdForward ? O : nullptr; dp.res = nullptr;
     dp.stage_elems = decode_stage_elems((int)C, (int)D, (int)Mp);
     dp.stage_bytes = (int)(dkind == kDecodePersist ? persist_stage_bytes((int)D, (int)Mp, (int)dtype_bytes(dtype))
                                                    : dec2_stage_bytes((int)C, (int)D, (int)Mp, (int)dtype_bytes(dtype)));
     dp.kind = dkind;
     HIPTRY(launch_decode_fused<T>(dp, (int)D, s));
     if (mode == kBwdForward) return ok();
-    }
   } else {
   RoutePrepParams sp{};
   sp.src = seeds; sp.src_bstride = 0; sp.B = 1; sp.H = (int)H; sp.M = (int)M; sp.Mp = (int)Mp;
@@ -874,10 +870,24 @@ int backward_impl(int dtype, int64_t B, int64_t N, int64_t C, int64_t H, int64_t
   CombineParams c2 = c1;
   c2.out32 = w.Zf; c2.lse = w.L2; c2.q_op = nullptr; c2.z_op = w.z_op;
   HIPTRY(launch_combine_par<T>(c2, s));
-  TRY(unfused_call3());
+  // call 3 (route operands as rows of Q(X) scaled and Z d-major) writes Y and
+  // the per-token log-normaliser
+  RouteParams r3 = decode_params(B, H, N, M, D);
+  r3.ka = w.q_op; r3.ka_sb = rtBS; r3.ka_sh = rtHS; r3.ka_rows = (int)Mp;
+  r3.va = w.z_op; r3.va_sb = H * D * Mp; r3.va_sh = D * Mp; r3.va_ld = (int)Mp;
+  r3.qs = w.K; r3.qs_sb = tokBS; r3.qs_sh = tokHS; r3.qs_rows = (int)N;
+  r3.y = w.Y; r3.y_sb = N * C; r3.y_row = C; r3.lse2 = w.L3;
+  HIPTRY(launch_route<T>(r3, (int)D, true, s));
   }
   }
   if (mode == kBwdForward) {  // the training forward's output O = Y W_O (the fused decode returned above)
+    if (w.wf[4]) {
+      ProjParams po{};
+      po.x = w.Y; po.B = (int)B; po.N = (int)N; po.Np = (int)Np; po.C = (int)C; po.H = (int)H; po.D = (int)D;
+      po.nw = 1; po.wf[0] = w.wf[4]; po.out[0] = O; po.layout[0] = kPlain;
+      HIPTRY(launch_project<T>(po, s));
+      return ok();
+    }
     GemmParams go{};
     go.M = (int)NT; go.N = (int)C; go.K = (int)C; go.nseg = 1; go.nprob = 1; go.splits = 1;
     go.a[0] = w.Y; go.a_m = C; go.a_k = 1;
@@ -888,12 +898,21 @@ int backward_impl(int dtype, int64_t B, int64_t N, int64_t C, int64_t H, int64_t
   }
 
   // ---- merge: dY = dO W_O^T (dW_O is computed with the weight gradients) ----
-  GemmParams g{};
-  g.M = (int)NT; g.N = (int)C; g.K = (int)C; g.nseg = 1; g.nprob = 1; g.splits = 1;
-  g.a[0] = dO; g.a_m = C; g.a_k = 1;
-  g.b[0] = Wo; g.b_k = 1; g.b_n = C;
-  g.kchunk = (int)round_up(C, 64); g.c = w.dY; g.c_t = 1; g.ldc = C; g.split_stride = 0;
-  HIPTRY(launch_gemm<T>(g, s));
+  if (w.wft[4]) {
+    // with it, -L and -c = -<dY, Y> of the decode's positions
+    ProjParams py{};
+    py.x = dO; py.B = (int)B; py.N = (int)N; py.Np = (int)Np; py.C = (int)C; py.H = (int)H; py.D = (int)D;
+    py.nw = 1; py.wf[0] = w.wft[4]; py.out[0] = w.dY; py.layout[0] = kPlain;
+    py.ydot = w.Y; py.lcol = w.L3; py.lc = w.lc;
+    HIPTRY(launch_project<T>(py, s));
+  } else {
+    GemmParams g{};
+    g.M = (int)NT; g.N = (int)C; g.K = (int)C; g.nseg = 1; g.nprob = 1; g.splits = 1;
+    g.a[0] = dO; g.a_m = C; g.a_k = 1;
+    g.b[0] = Wo; g.b_k = 1; g.b_n = C;
+    g.kchunk = (int)round_up(C, 64); g.c = w.dY; g.c_t = 1; g.ldc = C; g.split_stride = 0;
+    HIPTRY(launch_gemm<T>(g, s));
+  }
 
   // one SDPA backward, launched once per window of route blocks; the later
   // windows add to the long-side gradients of the earlier ones
@@ -911,11 +930,6 @@ int backward_impl(int dtype, int64_t B, int64_t N, int64_t C, int64_t H, int64_t
 
   if (rs_ok((int)D, (int)sizeof(T))) {
     // ---- the three calls with the route side in registers ----
-    const int Ns = (int)round_up(N, 512);
-    BwdRowdotParams rp{};
-    rp.dy = w.dY; rp.y = w.Y; rp.lcol = w.L3; rp.lc = w.lc;
-    rp.B = (int)B; rp.H = (int)H; rp.N = (int)N; rp.Ns = Ns;
-    HIPTRY(launch_bwd_rowdot(rp, (int)D, s));
     // one launch per window of route blocks; the later ones add to the
     // position-side gradients of the earlier ones
     auto windows = [&](const AttnBwdRsParams& a, bool dec) -> int {
@@ -932,7 +946,7 @@ int backward_impl(int dtype, int64_t B, int64_t N, int64_t C, int64_t H, int64_t
       return FLAREPP_OK;
     };
     AttnBwdRsParams a3{};
-    a3.B = (int)B; a3.H = (int)H; a3.N = (int)N; a3.M = (int)M; a3.Mp = (int)Mp; a3.Np = (int)Np; a3.Ns = Ns;
+    a3.B = (int)B; a3.H = (int)H; a3.N = (int)N; a3.M = (int)M; a3.Mp = (int)Mp; a3.Np = (int)Np;
     a3.s = sc; a3.sl2 = sc * 1.4426950408889634f;
     a3.q = w.Qf; a3.q_f32 = 1; a3.q_sb = H * M * D; a3.q_sh = M * D;
     a3.k = w.K; a3.dk = w.dK;
@@ -1043,6 +1057,39 @@ int backward_impl(int dtype, int64_t B, int64_t N, int64_t C, int64_t H, int64_t
 
   // ---- projections: dX = sum_j dG_j W_j^T; the weight gradients
   // dW_j = X^T dG_j and dW_O = Y^T dO in one split-K launch ----
+  if (grad_gemm_ok((int)C, (int)sizeof(T))) {
+    RowsSumParams rx{};
+    const void* G4[4] = {w.dK, w.dV, w.dKt, w.dVt};
+    for (int j = 0; j < 4; ++j) { rx.in[j] = G4[j]; rx.wf[j] = w.wft[j]; }
+    rx.out = dX; rx.T = NT;
+    HIPTRY(launch_rows_sum(rx, (int)C, s));
+    // the value gradients' low parts are problems of their own, added to the
+    // high parts' in the sum; tied weights (no dWkt) sum both of their uses
+    WgradParams gp{};
+    const void* wa7[7] = {X, X, X, X, w.Y, X, X};
+    const void* wb7[7] = {w.dK, w.dV, w.dKt, w.dVt, dO, w.dVlo, w.dVtlo};
+    for (int j = 0; j < w.wg_prob; ++j) { gp.a[j] = wa7[j]; gp.b[j] = wb7[j]; }
+    gp.part = w.gpart; gp.T = NT; gp.chunk = w.wg_chunk; gp.nprob = w.wg_prob; gp.nchunks = w.splits;
+    HIPTRY(launch_wgrad(gp, (int)C, s));
+    WgradSumParams sm{};
+    sm.part = w.gpart; sm.nchunks = w.splits; sm.n = C * C;
+    auto sum_of = [&](float* out, std::initializer_list<int> probs) {
+      sm.out[sm.nout] = out;
+      int k = 0;
+      for (int q : probs)
+        if (q < w.wg_prob) sm.prob[sm.nout][k++] = q;
+      if (k < 4) sm.prob[sm.nout][k] = -1;
+      ++sm.nout;
+    };
+    if (dWkt) {
+      sum_of(dWk, {0}); sum_of(dWv, {1, 5}); sum_of(dWkt, {2}); sum_of(dWvt, {3, 6});
+    } else {
+      sum_of(dWk, {0, 2}); sum_of(dWv, {1, 3, 5, 6});
+    }
+    sum_of(dWo, {4});
+    HIPTRY(launch_wgrad_sum(sm, s));
+    return ok();
+  }
   GemmParams gx{};
   gx.M = (int)NT; gx.N = (int)C; gx.K = (int)C; gx.nseg = 4; gx.nprob = 1; gx.splits = 1;
   const void* G[4] = {w.dK, w.dV, w.dKt, w.dVt};

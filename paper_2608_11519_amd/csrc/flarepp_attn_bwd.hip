@@ -52,7 +52,6 @@ namespace {
 
 constexpr float kLog2e = 1.4426950408889634f;
 typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
-typedef __attribute__((ext_vector_type(4))) short s16x4;
 
 __device__ __forceinline__ f32x16 mfma32(const bf16x8& a, const bf16x8& b, const f32x16& c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
@@ -66,19 +65,6 @@ __device__ __forceinline__ f32x4 mfma16(const bf16x8& a, const bf16x8& b, const 
 __device__ __forceinline__ f32x16 mfma_rows(const s16x4& a, const s16x4& b, const f32x16& c) {
   return __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(a, b, c, 0, 0, 0);
 }
-// x as three bf16 terms (24 bits, all of x's) for the lanes of k slots 0 .. 3
-__device__ __forceinline__ s16x4 split3(float x) {
-  bf16x4 r;
-  r[0] = (__bf16)x;
-  x -= (float)r[0];
-  r[1] = (__bf16)x;
-  x -= (float)r[1];
-  r[2] = (__bf16)x;
-  r[3] = (__bf16)0.f;
-  return __builtin_bit_cast(s16x4, r);
-}
-constexpr float kNoMass = -1e30f;  // log2 weight of an excluded route or position (finite: times 0 is 0)
-
 // k order of the operands made from a 32 x 32 result (lane row r4 = lane / 16,
 // element j): of the 16-column operands after the swap, and of a transposed
 // 16 x 16 pair.
@@ -113,31 +99,6 @@ __device__ __forceinline__ bf16x8 pack8(const f32x16& a, int o) {
 #pragma unroll
   for (int j = 0; j < 8; ++j) r[j] = (__bf16)a[o + j];
   return r;
-}
-
-// Two transposing LDS reads (16 lanes read 4 rows x 16 columns, lane i comes
-// out with column i of the 4 rows): elements 0 .. 3 from p0, 4 .. 7 from p1.
-__device__ __forceinline__ bf16x8 tr_frag(const __bf16* p0, const __bf16* p1) {
-  typedef __attribute__((address_space(3))) s16x4* lp;
-  const s16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lp)(void*)p0);
-  const s16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lp)(void*)p1);
-  bf16x8 r;
-  const bf16x4 x = __builtin_bit_cast(bf16x4, a), y = __builtin_bit_cast(bf16x4, b);
-#pragma unroll
-  for (int j = 0; j < 4; ++j) { r[j] = x[j]; r[4 + j] = y[j]; }
-  return r;
-}
-
-// 16 bytes per lane, global -> LDS at dst + 16 lane (dst wave-uniform).  As
-// assembly (it has no register output) because the compiler, which cannot
-// tell the two stage buffers apart, otherwise waits for every copy in flight
-// before any LDS read; the kernel waits once per step, ahead of its barrier.
-__device__ __forceinline__ void dma16(const void* src, char* dst) {
-  const unsigned off = __builtin_amdgcn_readfirstlane(
-      (unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)dst);
-  unsigned m0;
-  asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off\n\ts_mov_b32 m0, %0"
-               : "=&s"(m0) : "v"(src), "s"(off) : "memory");
 }
 
 // Tiles per position group and step, and 16-byte pieces per tile and lane of
@@ -206,13 +167,13 @@ __global__ __launch_bounds__(512) void k_attn_bwd_rs(AttnBwdRsParams p) {
         const int64_t n = min(t0 + c, (int64_t)p.N - 1);
         src = (second ? gx + n * p.g_sn : kx + n * D) + 16 * sub + 8 * g;
       }
-      dma16(src, dst + q * 1024);
+      lds_copy16(src, dst + q * 1024);
     }
     if constexpr (DEC) {
       // 16 bytes of every position: -L and -c as three bf16 terms each
-      const char* src = static_cast<const char*>(p.lc) + ((int64_t)bh * p.Ns + n0) * 16;
+      const char* src = static_cast<const char*>(p.lc) + (int64_t)bh * p.N * 16;
       for (int o = 64 * wave; o < SP; o += 512)
-        if (o + lane < SP) dma16(src + (o + lane) * 16, dst + 4 * SP * D + 16 * o);
+        if (o + lane < SP) lds_copy16(src + min(n0 + o + lane, (int64_t)p.N - 1) * 16, dst + 4 * SP * D + 16 * o);
     }
   };
   if (nsteps > 0) stage_issue(0);
@@ -386,15 +347,16 @@ __global__ __launch_bounds__(512) void k_attn_bwd_rs(AttnBwdRsParams p) {
     for (int ks = 0; ks < KS; ++ks) {
       t.kb[ks] = load_frag(sk + row_off + ks * 512);
       if (DEC) t.gb[ks] = load_frag(sg + row_off + ks * 512);
-      else t.gb[ks] = tr_frag(sg + v_off + ks * 512, sg + v_off + ks * 512 + 128);
+      else t.gb[ks] = lds_tr_frag(sg + v_off + ks * 512, sg + v_off + ks * 512 + 128);
     }
 #pragma unroll
     for (int kk = 0; kk < NK; ++kk) {
-      t.kt[kk] = tr_frag(sk + tr_off0 + kk * 128, sk + tr_off1 + kk * 128);
-      if (DEC) t.yt[kk] = tr_frag(sg + tr_off0 + kk * 128, sg + tr_off1 + kk * 128);
+      t.kt[kk] = lds_tr_frag(sk + tr_off0 + kk * 128, sk + tr_off1 + kk * 128);
+      if (DEC) t.yt[kk] = lds_tr_frag(sg + tr_off0 + kk * 128, sg + tr_off1 + kk * 128);
     }
-    // encode: a position past N repeats the last row, so its P is at most 1
-    // and its dS finite; zero keys keep it out of dQ
+    // A position past N repeats the last row.  Encode: its P is at most 1 and
+    // its dS finite, and zero keys keep it out of dQ; decode: without mass its
+    // P is zero.
     const int64_t left = p.N - (pos0 + (int64_t)st * SP + 32 * tile);  // uniform
     if (!DEC && left < 32) {
       int r = r4;
@@ -410,6 +372,7 @@ __global__ __launch_bounds__(512) void k_attn_bwd_rs(AttnBwdRsParams p) {
       const s16x8 x = *reinterpret_cast<const s16x8*>(sk + (2 * SP - tile * 32) * D + (32 * tile + c) * 8);
       t.l = s16x4{x[0], x[1], x[2], x[3]};
       t.c = s16x4{x[4], x[5], x[6], x[7]};
+      if (left < 32 && c >= left) t.l = s16x4{split3(kNoMass)[0], 0, 0, 0};  // past N: no mass
     }
   };
   // dS^T: the lane's two runs of 8 queries' dS go to a 2 KiB scratch as rows
@@ -565,8 +528,8 @@ __global__ __launch_bounds__(512) void k_attn_bwd_rs(AttnBwdRsParams p) {
       __builtin_amdgcn_sched_barrier(0);
       if (k + 1 < K) value(k + 1);
       if constexpr (D == 16) {
-        t0 = tr_frag(x0 + x_off, x0 + x_off + 256);
-        t1 = tr_frag(x1 + x_off, x1 + x_off + 256);
+        t0 = lds_tr_frag(x0 + x_off, x0 + x_off + 256);
+        t1 = lds_tr_frag(x1 + x_off, x1 + x_off + 256);
         swap_cols(p0, p1);
         swap_cols(d0, d1);
         if constexpr (DEC) {
@@ -583,8 +546,8 @@ __global__ __launch_bounds__(512) void k_attn_bwd_rs(AttnBwdRsParams p) {
       } else {
         // the half of the columns that this lane's row of 16 reads
         const T* xh = (r4 & 1) ? x1 : x0;
-        t0 = tr_frag(xh + x_off, xh + x_off + 128);
-        t1 = tr_frag(xh + x_off + 256, xh + x_off + 384);
+        t0 = lds_tr_frag(xh + x_off, xh + x_off + 128);
+        t1 = lds_tr_frag(xh + x_off + 256, xh + x_off + 384);
         if constexpr (DEC) {
           add16(az[i], t.yt[0], p0, t.yt[1], p1);
           add16(aq[i], t.kt[0], d0, t.kt[1], d1);
@@ -649,36 +612,6 @@ __global__ __launch_bounds__(512) void k_attn_bwd_rs(AttnBwdRsParams p) {
   }
 }
 
-// Decode: -L and -c = -<dY_n, Y_n> of every (b, h, n) as three bf16 terms
-// each, [B * H][Ns][8], the
-// positions past N without mass, so that their P is
-// zero.  One thread per
-// (token, run of 8 channels); a head's runs are neighbouring lanes.
-template <int D>
-__global__ __launch_bounds__(256) void k_bwd_rowdot(BwdRowdotParams p) {
-  const int RUNS = p.H * (D / 8);
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const int64_t bn = i / RUNS;
-  const int run = (int)(i % RUNS), h = run / (D / 8);
-  if (bn >= (int64_t)p.B * p.Ns) return;
-  const int b = (int)(bn / p.Ns), n = (int)(bn % p.Ns);
-  float s = 0.f;
-  if (n < p.N) {
-    const int64_t o = ((int64_t)b * p.N + n) * (p.H * D) + run * 8;
-    const bf16x8 x = load_frag(static_cast<const __bf16*>(p.dy) + o), y = load_frag(static_cast<const __bf16*>(p.y) + o);
-#pragma unroll
-    for (int j = 0; j < 8; ++j) s += (float)x[j] * (float)y[j];
-  }
-  s += __shfl_xor(s, 1, 64);
-  if (D == 32) s += __shfl_xor(s, 2, 64);
-  if (run % (D / 8) == 0) {
-    const int64_t o = ((int64_t)b * p.H + h) * p.Ns + n;
-    s16x4* out = static_cast<s16x4*>(p.lc) + 2 * o;
-    out[0] = split3(n < p.N ? -p.lcol[((int64_t)b * p.H + h) * p.N + n] : kNoMass);
-    out[1] = split3(-s);
-  }
-}
-
 template <int D, bool DEC, int RB>
 hipError_t rs_go(const AttnBwdRsParams& p, hipStream_t s) {
   const int rw = 1 << p.rw_log2;
@@ -730,13 +663,6 @@ hipError_t launch_attn_bwd_rs(const AttnBwdRsParams& p, int D, bool dec, int rb,
   }
   if (rb == 2) return dec ? rs_go<32, true, 2>(p, s) : rs_go<32, false, 2>(p, s);
   return dec ? rs_go<32, true, 1>(p, s) : rs_go<32, false, 1>(p, s);
-}
-
-hipError_t launch_bwd_rowdot(const BwdRowdotParams& p, int D, hipStream_t s) {
-  const int64_t n = (int64_t)p.B * p.Ns * p.H * (D / 8);
-  if (D == 16) k_bwd_rowdot<16><<<(unsigned)((n + 255) / 256), 256, 0, s>>>(p);
-  else k_bwd_rowdot<32><<<(unsigned)((n + 255) / 256), 256, 0, s>>>(p);
-  return hipGetLastError();
 }
 
 }  // namespace flarepp

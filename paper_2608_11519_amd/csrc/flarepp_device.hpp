@@ -18,6 +18,7 @@ namespace flarepp {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
+typedef __attribute__((ext_vector_type(4))) short s16x4;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(8))) float f32x8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
@@ -149,6 +150,18 @@ __device__ __forceinline__ void store16(T* op, const f32x16& o, const Res16<T>& 
   }
 }
 
+// x as three bf16 terms (24 bits, all of x's), the fourth zero
+__device__ __forceinline__ s16x4 split3(float x) {
+  bf16x4 r;
+  r[0] = (__bf16)x;
+  x -= (float)r[0];
+  r[1] = (__bf16)x;
+  x -= (float)r[1];
+  r[2] = (__bf16)x;
+  r[3] = (__bf16)0.f;
+  return __builtin_bit_cast(s16x4, r);
+}
+
 // ---- LDS staging ---------------------------------------------------------------
 // Wait for every vector memory load of the wave (the copies into LDS among
 // them), then a workgroup barrier.
@@ -185,6 +198,30 @@ __device__ __forceinline__ void copy_to_lds(const void* src, char* dst, int n16,
           rsrc, (__attribute__((address_space(3))) void*)(dst + (size_t)(k * nt + wave * 64) * 16), 16, toff,
           k * nt * 16, 0, 0);
   }
+}
+
+// 16 bytes per lane, global -> LDS at dst + 16 lane (dst wave-uniform).  As
+// assembly (it has no register output) because the compiler, which cannot
+// tell the buffers of a ring apart, waits for every copy in flight before any
+// LDS read; a kernel that uses it waits by count ahead of its barriers.
+__device__ __forceinline__ void lds_copy16(const void* src, char* dst) {
+  const unsigned off = __builtin_amdgcn_readfirstlane(
+      (unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)dst);
+  unsigned m0;
+  asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off\n\ts_mov_b32 m0, %0"
+               : "=&s"(m0) : "v"(src), "s"(off) : "memory");
+}
+
+// Two transposing LDS reads (16 lanes read 4 rows x 16 columns, lane i comes
+// out with column i of the 4 rows): elements 0 .. 3 from p0, 4 .. 7 from p1.
+__device__ __forceinline__ bf16x8 lds_tr_frag(const void* p0, const void* p1) {
+  typedef __attribute__((address_space(3))) s16x4* lp;
+  const bf16x4 x = __builtin_bit_cast(bf16x4, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lp) const_cast<void*>(p0)));
+  const bf16x4 y = __builtin_bit_cast(bf16x4, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lp) const_cast<void*>(p1)));
+  bf16x8 r;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) { r[j] = x[j]; r[4 + j] = y[j]; }
+  return r;
 }
 
 // ---- cross-lane helpers ------------------------------------------------------

@@ -824,8 +824,6 @@ __global__ __launch_bounds__(256) void k_combine_par(CombineParams p) {
       if (k == d) v = a[k];
     const float out = v * inv;
     if (valid && p.out32) p.out32[(bh * p.M + qrow) * D + d] = out;
-    if (p.q_rows) ((T*)p.q_rows)[(bh * p.Mp + qrow) * D + d] = from_f32<T>(out * p.qscale);
-    if (p.z_rows) ((T*)p.z_rows)[(bh * D + d) * p.Mp + qrow] = from_f32<T>(out);
     if (!p.frag) {
       if (p.q_op) ((T*)p.q_op)[(bh * p.Mp + qrow) * D + d] = from_f32<T>(out * p.qscale);
       if (p.z_op) ((T*)p.z_op)[(bh * D + d) * p.Mp + qrow] = from_f32<T>(out);
@@ -849,6 +847,23 @@ __global__ __launch_bounds__(256) void k_combine_par(CombineParams p) {
     if (i >= p.prep_n) break;
     prep_store<T>(p.prep, i, prep_load<T>(p.prep, i));
   }
+}
+
+// A token's decoded row from its merge operands: fragment i holds channels
+// 16 i + 8 (j / 4) + 4 g + j % 4.  All heads together after the last one:
+// stored per head, the next stage's barrier would wait for them right away.
+template <typename T, int KSC>
+__device__ __forceinline__ void store_decoded(T* yp, const typename Frag<T>::type (&yf)[KSC], int g) {
+  using Half = typename Frag<T>::half;
+#pragma unroll
+  for (int i = 0; i < KSC; ++i)
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      Half v;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = yf[i][4 * q + e];
+      *reinterpret_cast<Half*>(yp + 16 * i + 8 * q + 4 * g) = v;
+    }
 }
 
 // Route tiles of the HPG heads of a group, software pipelined over the
@@ -1100,20 +1115,11 @@ __global__ __launch_bounds__(64 * dec_waves(16 * KSC)) void k_decode_fused(DecFu
       // log2 of the softmax normaliser over the routes (0 is the shift of the
       // shift-free tiles), for the backward
       if (p.lse2 && xok && g == 0) p.lse2[((int64_t)b * H + (h)) * p.N + xrow] = (fast ? 0.f : m[hh]) + __log2f(den);
-      if (p.y && xok) {
-        T* yp = (T*)p.y + ((int64_t)b * p.N + xrow) * C + h * D;
-        constexpr int NQ4 = ONES_ROW ? 2 : 4;
-#pragma unroll
-        for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-          for (int q = 0; q < NQ4; ++q)
-            store4(yp + rb * 32 + 8 * q + 4 * g, acc[hh][rb][4 * q] * inv, acc[hh][rb][4 * q + 1] * inv,
-                   acc[hh][rb][4 * q + 2] * inv, acc[hh][rb][4 * q + 3] * inv);
-      }
     }
     lds_wait_barrier();
   }
-
+  if (p.y && xok) store_decoded<T, KSC>((T*)p.y + ((int64_t)b * p.N + xrow) * C, yf, g);
+  if (!p.o) return;  // the backward's forward needs Y alone (uniform; every copy has landed)
   // ---- merge: O^T = W_O^T Y^T, one 32-channel output block per stage ----
   // A block's stores are issued after the next barrier, and its residual is
   // loaded before its stage's copy: the barrier's wait for the next stage's
@@ -1431,7 +1437,7 @@ __global__ __launch_bounds__(64 * dec_waves(16 * KSC)) void k_decode2(DecFusedPa
     if (!RES && hg + 1 < HG) lds_wait_barrier();  // next stage in; this one free
   }
 
-  if (xok) {
+  if (xok && p.o) {
     const int64_t oo = ((int64_t)b * p.N + xrow) * C;
     Res16<T> res[CB];
     if (p.res) {
@@ -1746,6 +1752,7 @@ __global__ __launch_bounds__(64 * dec_waves(16 * KSC)) void k_decode3(DecFusedPa
       }
     }
   }
+  if (!p.o) return;  // the backward's forward needs Y alone
   // merge: output block cb of O^T = sum over the groups of W_O^T rows x Y^T
   // (the residual of every block is loaded before the first MFMA)
   const int64_t oo = ((int64_t)b * p.N + xrow) * C;
@@ -1860,6 +1867,9 @@ __global__ __launch_bounds__(64 * dec_waves(16 * KSC)) void k_decode_persist(Dec
     const int tn = t + gridDim.x;  // the next token block of this workgroup
     F yf[KSC];                     // decoded tokens, oldest group first (shift register)
     bool xpending = false;         // the next block's X loads are in flight
+    // each head ends with one store of its tokens' normalisers (on any lane)
+    const bool lstore = p.lse2 && uniform((t % nblk) * TOK + wave * 32 < p.N);
+    bool lpending = false;
     for (int hg = 0; hg < HG; ++hg) {
       // key projection of the group's heads from the resident W_K slice
       f32x16 ka[GB];
@@ -1888,10 +1898,13 @@ __global__ __launch_bounds__(64 * dec_waves(16 * KSC)) void k_decode_persist(Dec
         // every wave is done with the previous one, whose buffer takes the
         // next.  Only the KSC loads of the next block's X rows (issued after
         // the copy, see below) may stay in flight across the barrier.
+        // (and, for the backward, the previous head's store of the normalisers)
         if (xpending) {
-          asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(KSC) : "memory");
+          if (lpending) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(KSC + 1) : "memory");
+          else asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(KSC) : "memory");
         } else {
-          asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+          if (lpending) asm volatile("s_waitcnt vmcnt(1) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+          else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
         }
         const int buf = seq & 1;
         ++seq;
@@ -1955,18 +1968,12 @@ __global__ __launch_bounds__(64 * dec_waves(16 * KSC)) void k_decode_persist(Dec
         // log2 of the softmax normaliser over the routes (0 is the shift of the
         // shift-free tiles), for the backward
         if (p.lse2 && xok && g == 0) p.lse2[((int64_t)b * H + (h)) * p.N + xrow] = (fast ? 0.f : m) + __log2f(den);
-        if (p.y && xok) {
-          T* yp = (T*)p.y + ((int64_t)b * p.N + xrow) * C + h * D;
-          constexpr int NQ4 = ONES_ROW ? 2 : 4;
-#pragma unroll
-          for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-            for (int q = 0; q < NQ4; ++q)
-              store4(yp + rb * 32 + 8 * q + 4 * g, acc[rb][4 * q] * inv, acc[rb][4 * q + 1] * inv,
-                     acc[rb][4 * q + 2] * inv, acc[rb][4 * q + 3] * inv);
-        }
+        lpending = lstore;  // the head's only access since its copy and X loads
       }
     }
+    lpending = false;  // the stores below follow: the next barrier waits for all
+    if (p.y && xok) store_decoded<T, KSC>((T*)p.y + ((int64_t)b * p.N + xrow) * C, yf, g);
+    if (!p.o) continue;  // the backward's forward needs Y alone
     // merge: output block cb of O^T = sum over the groups of W_O^T rows x Y^T
     // (the residual of every block is loaded before the first MFMA)
     const int64_t oo = ((int64_t)b * p.N + xrow) * C;

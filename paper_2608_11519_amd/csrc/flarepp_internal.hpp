@@ -10,8 +10,9 @@ enum ProjLayout { kHeadsTokenMajor = 0, kHeadsDMajor = 1, kPlain = 2 };
 
 struct WeightFragParams {
   int C, nw;
-  const void* w[5];
-  void* out[5];
+  const void* w[10];
+  void* out[10];
+  int trans[10];  // fragments of W^T (out = X W^T)
 };
 
 struct RoutePrepParams {
@@ -37,6 +38,10 @@ struct ProjParams {
   void* out[5];
   int layout[5];
   const void* res;  // kPlain outputs: [B][N][C] added to the product, or null
+  // plain output dY (bf16, D = 16 or 32) with ydot = Y [B][N][C]: also -L and
+  // -c = -<dY, Y> of every head, as three bf16 terms each, to lc [B * H][N][8];
+  // lcol [B * H][N] is L (log2)
+  const void* ydot; const float* lcol; void* lc;
 };
 
 // Layer normalisation over the channels of every token: y = (x - mean) /
@@ -107,10 +112,6 @@ struct CombineParams {
   void* z_op;
   float* qnorm2;  // frag == 1 with q_op: [BH][Mp / 4] max of |scaled q|^2 over
                   // each group of 4 routes (one entry per wave), or null
-  // the frag == 0 layouts as well, whatever frag is (the backward's unfused
-  // decode after fused encodes): q_rows [BH][Mp][D] scaled, z_rows [BH][D][Mp]
-  void* q_rows;
-  void* z_rows;
   // fragment conversion for the later kernels (prep_n items), spread over the
   // threads: each issues its item's loads first and stores it at the end
   PrepFusedParams prep;
@@ -165,7 +166,7 @@ struct DecFusedParams {
   float fast_lim;
   void* y;            // [B][N][C] decoded tokens, or null
   float* lse2;        // [B][H][N] log2 softmax normaliser of each token's scaled scores, or null
-  void* o;            // [B][N][C]
+  void* o;            // [B][N][C], or null (Y alone: no merge)
   const void* res;    // [B][N][C] added to O (the block's residual), or null
   int stage_elems;    // elements per LDS stage buffer (k_decode_fused)
   int stage_bytes;    // bytes per head-group stage (k_decode2)
@@ -280,7 +281,7 @@ struct AttnBwdParams {
 // (flarepp_attn_bwd.hip): a launch covers nb route blocks from sb0, chunks of
 // `steps` steps of positions per workgroup, R chunks per (b, h).
 struct AttnBwdRsParams {
-  int B, H, N, M, Mp, Np, Ns, R, steps;  // Np, Ns: N rounded up to 32, 512
+  int B, H, N, M, Mp, Np, R, steps;  // Np: N rounded up to 32
   int sb0, nb, rw_log2;                  // rw_log2: log2 of the route groups of a workgroup
   float s, sl2;                          // 1/sqrt(D), and times log2(e)
   const void* q; int q_f32; int64_t q_sb, q_sh;  // [M][D] per (b, h): Q, or the seeds (fp32 or bf16)
@@ -289,7 +290,7 @@ struct AttnBwdRsParams {
   const float* lse;  // encode: [B * H][M] natural-log normaliser
   const void* k;     // [B * H][N][D]
   const void* g; int64_t g_sb, g_sh, g_sn;  // encode: V d-major [B * H][D][Np]; decode: dY rows
-  const void* lc;    // decode: -L (log2) and -c as three bf16 terms each, [B * H][Ns][8]
+  const void* lc;    // decode: -L (log2) and -c as three bf16 terms each, [B * H][N][8]
   // gradients as for AttnBwdParams: dk (both), dg with its low part (encode)
   void* dk; int acc_k;
   void* dg; void* dg_lo; int acc_g;
@@ -302,14 +303,36 @@ struct RsSplit {
 constexpr bool rs_ok(int D, int elem_bytes) { return elem_bytes == 2 && (D == 16 || D == 32); }
 RsSplit rs_split(int64_t B, int64_t H, int64_t N, int D, int Mp);
 hipError_t launch_attn_bwd_rs(const AttnBwdRsParams&, int D, bool dec, int rb, hipStream_t);
-// -L and -c of the decode's positions for the kernel above
-struct BwdRowdotParams {
-  const void* dy; const void* y;  // [B][N][H * D]
-  const float* lcol;              // [B * H][N]
-  void* lc;                       // [B * H][Ns][8] bf16
-  int B, H, N, Ns;
+constexpr float kNoMass = -1e30f;  // log2 weight of an excluded route or position (finite: times 0 is 0)
+
+// Weight gradients (bf16, C = 64, 128 or 256): problem j's partials over token
+// chunk r, part[j][r][C][C] = a[j]^T b[j] over the chunk's rows ([T][C] each).
+struct WgradParams {
+  const void* a[7]; const void* b[7];
+  float* part;
+  int64_t T, chunk;  // tokens per chunk, a multiple of 32
+  int nprob, nchunks;
 };
-hipError_t launch_bwd_rowdot(const BwdRowdotParams&, int D, hipStream_t);
+// out[o] = sum over its problems prob[o][0 ..] (ended by -1) and their chunks
+struct WgradSumParams {
+  const float* part;
+  float* out[5];
+  int prob[5][4];
+  int nout, nchunks;
+  int64_t n;  // C * C
+};
+// out [T][C] (fp32) = sum of in[j] [T][C] times the transposed weight with
+// fragments wf[j], j < 4
+struct RowsSumParams {
+  const void* in[4]; const void* wf[4];
+  float* out;
+  int64_t T;
+};
+constexpr bool grad_gemm_ok(int C, int elem_bytes) { return elem_bytes == 2 && (C == 64 || C == 128 || C == 256); }
+int wgrad_chunks(int64_t T, int C, int nprob, int64_t* chunk);
+hipError_t launch_wgrad(const WgradParams&, int C, hipStream_t);
+hipError_t launch_wgrad_sum(const WgradSumParams&, hipStream_t);
+hipError_t launch_rows_sum(const RowsSumParams&, int C, hipStream_t);
 // LDS of a launch over a window of nsb route blocks (Mp routes in all)
 int attn_bwd_waves(int D, int nsb, int Mp, bool dec, int elem_bytes);
 size_t attn_bwd_lds_bytes(int D, int nsb, int Mp, bool dec, int waves, int elem_bytes);

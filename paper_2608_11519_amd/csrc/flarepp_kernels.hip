@@ -46,6 +46,10 @@ __global__ void k_weight_frags(WeightFragParams p) {
   const T* W = (const T*)p.w[w];
   T* out = (T*)p.out[w] + f * 8;
   const int col = 32 * cb + (lane & 31), k0 = 16 * ks + 8 * (lane >> 5);
+  if (p.trans[w]) {  // W^T
+    *reinterpret_cast<typename Frag<T>::type*>(out) = load_frag(W + (int64_t)col * C + k0);
+    return;
+  }
 #pragma unroll
   for (int j = 0; j < 8; ++j) out[j] = W[(int64_t)(k0 + j) * C + col];
 }
@@ -133,9 +137,50 @@ __device__ __forceinline__ void store8(float* p, const float (&v)[8]) {
   reinterpret_cast<f32x4*>(p)[1] = b;
 }
 
+// A plain output's second operand for one lane: its token's rows of the
+// residual or of Y, and with Y the log-normalisers, per output block.
+template <typename T, int NQ>
+struct ProjExtra {
+  Res16<T> r[NQ];
+  float l[NQ];
+};
+// (rows past N load row N - 1 and are not used)
+template <typename T, int NQ>
+__device__ __forceinline__ void load_extra(ProjExtra<T, NQ>& x, const ProjParams& p, int b, int xrow, int cb0, int g) {
+  const int n = min(xrow, p.N - 1), CB = p.C / 32;
+  const T* src = (const T*)(p.ydot ? p.ydot : p.res) + ((int64_t)b * p.N + n) * p.C;
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) {
+    if (cb0 + q >= CB) break;  // wave-uniform
+    load_res16(x.r[q], src + 32 * (cb0 + q), g);
+    if (p.ydot) x.l[q] = p.lcol[((int64_t)b * p.H + (p.D == 16 ? 2 * (cb0 + q) + g : cb0 + q)) * p.N + n];
+  }
+}
+
+// -L and -c = -<dY, Y> of the heads of output block cb (32 channels) for the
+// lane's token, from the block's dY (rounded as it is stored) in acc.
+__device__ __forceinline__ void row_terms(const ProjParams& p, int b, int xrow, int cb, const f32x16& acc,
+                                          const Res16<__bf16>& y, float l, int g) {
+  float s[2] = {0.f, 0.f};
+#pragma unroll
+  for (int e = 0; e < 16; ++e) s[e >> 3] += (float)(__bf16)acc[e] * (float)y.r[e >> 2][e & 3];
+  s[0] = halves_sum(s[0]);
+  s[1] = halves_sum(s[1]);
+  // D = 16: lanes 0 .. 31 store the first head, lanes 32 .. 63 the second
+  const bool two = p.D == 16;
+  if (xrow < p.N && (two || g == 0)) {
+    const int64_t o = ((int64_t)b * p.H + (two ? 2 * cb + g : cb)) * p.N + xrow;
+    s16x4* out = (s16x4*)p.lc + 2 * o;
+    out[0] = split3(-l);
+    out[1] = split3(two ? (g ? -s[1] : -s[0]) : -(s[0] + s[1]));
+  }
+}
+
+template <typename T, int NQ>
+struct ProjExtra;
 template <typename T, int NQ = kProjBlocks, int LAYOUT = -1>
 __device__ __forceinline__ void proj_store(const ProjParams& p, int b, int n0, int w, int cg,
-                                           const f32x16 (&acc)[NQ]);
+                                           const f32x16 (&acc)[NQ], const ProjExtra<T, NQ>* extra = nullptr);
 
 // One unit: tokens [n0, n0 + 32) of batch entry b times column group cg of
 // weight w, whose fragments start at wf (global memory or an LDS copy).
@@ -190,7 +235,7 @@ __device__ __forceinline__ void proj_unit(const ProjParams& p, int b, int n0, in
 // layout when known at compile time, else -1.
 template <typename T, int NQ, int LAYOUT>
 __device__ __forceinline__ void proj_store(const ProjParams& p, int b, int n0, int w, int cg,
-                                           const f32x16 (&acc)[NQ]) {
+                                           const f32x16 (&acc)[NQ], const ProjExtra<T, NQ>* extra) {
   int lane = lane_id();
   // computed again at each call: kept from being hoisted out of a caller's
   // loops, where the per-lane store offsets would occupy registers throughout
@@ -202,17 +247,12 @@ __device__ __forceinline__ void proj_store(const ProjParams& p, int b, int n0, i
   const bool xok = xrow < p.N;
   T* out = (T*)p.out[w];
   const int D = p.D;
-  // the residual of every block is loaded before the first store uses it
-  const bool has_res = layout == kPlain && p.res && xok;
-  Res16<T> res[NQ];
-  if (has_res) {
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-      const int cb = cg * NQ + q;
-      if (cb >= CB) break;  // wave-uniform
-      load_res16(res[q], (const T*)p.res + ((int64_t)b * p.N + xrow) * p.C + 32 * cb, g);
-    }
-  }
+  // the residual of every block is loaded before the first store uses it (or
+  // was by the caller)
+  const bool has_res = layout == kPlain && p.res && !p.ydot;
+  ProjExtra<T, NQ> own;
+  if (layout == kPlain && (p.res || p.ydot) && !extra) load_extra(own, p, b, xrow, cg * NQ, g);
+  const ProjExtra<T, NQ>& ex = extra ? *extra : own;
 #pragma unroll
   for (int q = 0; q < NQ; ++q) {
     const int cb = cg * NQ + q;
@@ -226,7 +266,10 @@ __device__ __forceinline__ void proj_store(const ProjParams& p, int b, int n0, i
       store8(o, r[0]);
       store8(o + 16, r[1]);
     } else if (layout == kPlain) {
-      if (xok) store16(out + ((int64_t)b * p.N + xrow) * p.C + 32 * cb, acc[q], res[q], has_res, g);
+      if (xok) store16(out + ((int64_t)b * p.N + xrow) * p.C + 32 * cb, acc[q], ex.r[q], has_res, g);
+      if constexpr (std::is_same<T, __bf16>::value) {
+        if (p.ydot) row_terms(p, b, xrow, cb, acc[q], ex.r[q], ex.l[q], g);  // uniform
+      }
     } else if (D % 8 == 0) {
       // rows = channels: two runs of 8 channels of one head per lane
       float r[2][8];
@@ -265,35 +308,48 @@ __global__ __launch_bounds__(256) void k_project(ProjParams p) {
 // One unit of the persistent form: the tile's X fragments xf times weight w
 // (fragments in LDS at wl), all CB = C / 32 column blocks, then the stores.
 // The d-major layout takes result rows = tokens, the others rows = channels.
+// Column blocks per pass (C = 256: two, next to the two tiles of X held).
+constexpr int proj_nq(int KS) { return KS > 8 ? 2 : KS / 2; }
+template <int KS>
+constexpr int proj_passes() { return KS / 2 / proj_nq(KS); }
+template <int KS> using ProjPassExtra = ProjExtra<__bf16, proj_nq(KS)>;
+
 template <int KS, int LAYOUT>
-__device__ __forceinline__ void proj_lds_unit(const ProjParams& p, int b, int n0, int w, const __bf16* wl,
-                                              const bf16x8 (&xf)[KS]) {
-  constexpr int CB = KS / 2;
-  const __bf16* wr = wl + lane_id() * 8;
-  f32x16 acc[CB];
+__device__ __forceinline__ void proj_lds_pass(const ProjParams& p, int b, int n0, int w, const __bf16* wl,
+                                              const bf16x8 (&xf)[KS], int cg, const ProjPassExtra<KS>* ex = nullptr) {
+  constexpr int NQ = proj_nq(KS);
+  const __bf16* wr = wl + (cg * NQ * KS * 64 + lane_id()) * 8;
+  f32x16 acc[NQ];
 #pragma unroll
-  for (int q = 0; q < CB; ++q)
+  for (int q = 0; q < NQ; ++q)
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[q][r] = 0.f;
 #pragma unroll
   for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
-    for (int q = 0; q < CB; ++q) {
+    for (int q = 0; q < NQ; ++q) {
       const bf16x8 wv = load_frag(wr + (q * KS + ks) * 512);
       if (LAYOUT == kHeadsDMajor) mma(acc[q], xf[ks], wv);
       else mma(acc[q], wv, xf[ks]);
     }
   // issue order: the LDS reads of k step ks + 1 go out before the products
-  // of step ks, and no further ahead (all of them hoisted would hold KS CB
+  // of step ks, and no further ahead (all of them hoisted would hold KS NQ
   // fragments in registers)
-  __builtin_amdgcn_sched_group_barrier(0x100, CB, 0);
+  __builtin_amdgcn_sched_group_barrier(0x100, NQ, 0);
 #pragma unroll
   for (int ks = 1; ks < KS; ++ks) {
-    __builtin_amdgcn_sched_group_barrier(0x100, CB, 0);
-    __builtin_amdgcn_sched_group_barrier(0x008, CB, 0);
+    __builtin_amdgcn_sched_group_barrier(0x100, NQ, 0);
+    __builtin_amdgcn_sched_group_barrier(0x008, NQ, 0);
   }
-  __builtin_amdgcn_sched_group_barrier(0x008, CB, 0);
-  proj_store<__bf16, CB, LAYOUT>(p, b, n0, w, 0, acc);
+  __builtin_amdgcn_sched_group_barrier(0x008, NQ, 0);
+  proj_store<__bf16, NQ, LAYOUT>(p, b, n0, w, cg, acc, ex);
+}
+
+template <int KS, int LAYOUT>
+__device__ __forceinline__ void proj_lds_unit(const ProjParams& p, int b, int n0, int w, const __bf16* wl,
+                                              const bf16x8 (&xf)[KS]) {
+#pragma unroll
+  for (int cg = 0; cg < proj_passes<KS>(); ++cg) proj_lds_pass<KS, LAYOUT>(p, b, n0, w, wl, xf, cg);
 }
 
 // Weight layout patterns of the persistent form (fixed at compile time so a
@@ -302,7 +358,9 @@ __device__ __forceinline__ void proj_lds_unit(const ProjParams& p, int b, int n0
 enum ProjPattern { kPatKV = 0, kPatTok = 1, kPatPlain = 2 };
 
 // Persistent form for bf16 when every weight's fragments fit in LDS together
-// (C = 16 KS <= 128): a workgroup of 8 waves per CU copies them in once, then
+// (C = 16 KS <= 128), or one weight per workgroup (C = 256, 128 KiB each; the
+// workgroups of one token stream are on one XCD and share its rows in L2): a
+// workgroup of 8 waves per CU copies them in once, then
 // each wave walks 32-token tiles (tile = blockIdx.x * 8 + wave, + 8
 // gridDim.x, ...).  A tile's rows of X stay in registers for all its units
 // (KS fragments) and the next tile's rows are loaded while the current one is
@@ -313,15 +371,17 @@ template <int KS, int PAT>
 __global__ __launch_bounds__(512) void k_project_lds(ProjParams p) {
   using T = __bf16;
   using F = Frag<T>::type;
-  constexpr int C = 16 * KS, CB = C / 32;  // one column group: CB <= kProjBlocks
-  static_assert(CB >= 1 && CB <= kProjBlocks, "C = 32 .. 32 kProjBlocks");
+  constexpr int C = 16 * KS;
+  constexpr bool ONE = C > 128;  // one weight per workgroup
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  for (int w = 0; w < p.nw; ++w)
-    copy_to_lds(p.wf[w], smem + (size_t)w * C * C * sizeof(T), C * C * (int)sizeof(T) / 16, 512);
+  const int L = blockIdx.x, w1 = ONE ? (L >> 3) % p.nw : 0, nl = ONE ? 1 : p.nw;
+  const int64_t stream = ONE ? (L >> 3) / p.nw * 8 + (L & 7) : L, streams = ONE ? gridDim.x / p.nw : gridDim.x;
+  for (int w = 0; w < nl; ++w)
+    copy_to_lds(p.wf[w1 + w], smem + (size_t)w * C * C * sizeof(T), C * C * (int)sizeof(T) / 16, 512);
   const int lane = lane_id(), g = lane >> 5, c = lane & 31;
   const int NB = p.Np / 32;
-  const int64_t tiles = (int64_t)p.B * NB, stride = (int64_t)gridDim.x * 8;
-  int64_t t = (int64_t)blockIdx.x * 8 + wave_id();
+  const int64_t tiles = (int64_t)p.B * NB, stride = streams * 8;
+  int64_t t = stream * 8 + wave_id();
   const __bf16* wl = reinterpret_cast<const __bf16*>(smem);
   // rows past N load row N - 1 and are zeroed before use (the d-major layout
   // stores them as the zero padding)
@@ -338,23 +398,42 @@ __global__ __launch_bounds__(512) void k_project_lds(ProjParams p) {
   auto tile = [&](F (&xf)[KS], F (&xn)[KS], int64_t tt) {
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) asm volatile("; x tile %0" : "+v"(xf[ks]));
-    if (tt + stride < tiles) load_tile(xn, tt + stride);
     const int b = (int)(tt / NB), n0 = (int)(tt % NB) * 32;
+    if (PAT != kPatPlain && tt + stride < tiles) load_tile(xn, tt + stride);
     if (n0 + c >= p.N) {
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) xf[ks] = zero_frag<T>();
     }
-    if constexpr (PAT == kPatKV) {
+    if constexpr (PAT == kPatPlain) {
+      // a second operand (residual or Y) goes out ahead of the next tile's
+      // rows, so that waiting for it does not wait for them (C = 256 has no
+      // registers for both: one pass of it at a time, the rows at the end)
+      constexpr int NP = proj_passes<KS>(), G = ONE ? 1 : NP;  // passes, passes per group
+      const bool has_ex = p.res || p.ydot;                     // uniform
+#pragma unroll
+      for (int c0 = 0; c0 < NP; c0 += G) {
+        ProjPassExtra<KS> ex[G];
+        if (has_ex) {
+#pragma unroll
+          for (int k = 0; k < G; ++k) load_extra(ex[k], p, b, n0 + c, (c0 + k) * proj_nq(KS), g);
+        }
+        if (!ONE && tt + stride < tiles) load_tile(xn, tt + stride);
+#pragma unroll
+        for (int k = 0; k < G; ++k) proj_lds_pass<KS, kPlain>(p, b, n0, w1, wl, xf, c0 + k, &ex[k]);
+      }
+      if (ONE && tt + stride < tiles) load_tile(xf, tt + stride);
+    } else if constexpr (ONE) {
+      if (PAT == kPatKV && (w1 & 1)) proj_lds_unit<KS, kHeadsDMajor>(p, b, n0, w1, wl, xf);
+      else proj_lds_unit<KS, kHeadsTokenMajor>(p, b, n0, w1, wl, xf);
+    } else if constexpr (PAT == kPatKV) {
       proj_lds_unit<KS, kHeadsTokenMajor>(p, b, n0, 0, wl, xf);
       proj_lds_unit<KS, kHeadsDMajor>(p, b, n0, 1, wl + C * C, xf);
       if (p.nw == 4) {
         proj_lds_unit<KS, kHeadsTokenMajor>(p, b, n0, 2, wl + 2 * C * C, xf);
         proj_lds_unit<KS, kHeadsDMajor>(p, b, n0, 3, wl + 3 * C * C, xf);
       }
-    } else if constexpr (PAT == kPatTok) {
-      for (int w = 0; w < p.nw; ++w) proj_lds_unit<KS, kHeadsTokenMajor>(p, b, n0, w, wl + w * C * C, xf);
     } else {
-      proj_lds_unit<KS, kPlain>(p, b, n0, 0, wl, xf);
+      for (int w = 0; w < p.nw; ++w) proj_lds_unit<KS, kHeadsTokenMajor>(p, b, n0, w, wl + w * C * C, xf);
     }
   };
   // two register sets, alternating (no copies between tiles)
@@ -366,6 +445,10 @@ __global__ __launch_bounds__(512) void k_project_lds(ProjParams p) {
   // whole tile of stores
 #pragma unroll
   for (int ks = 0; ks < KS; ++ks) asm volatile("; x tile %0" : "+v"(xa[ks]));
+  if constexpr (ONE && PAT == kPatPlain) {
+    for (; t < tiles; t += stride) tile(xa, xa, t);
+    return;
+  }
   while (t < tiles) {
     tile(xa, xb, t);
     t += stride;
@@ -857,13 +940,15 @@ hipError_t launch_project(const ProjParams& p, hipStream_t s) {
     }
     pat = kv ? kPatKV : tok ? kPatTok : (p.nw == 1 && p.layout[0] == kPlain) ? kPatPlain : -1;
   }
-  const size_t lds = (size_t)p.nw * p.C * p.C * sizeof(T);
-  if (std::is_same<T, __bf16>::value && (p.C == 64 || p.C == 128) && lds <= 160 * 1024 && pat >= 0) {
+  const bool one = p.C == 256;  // one weight per workgroup
+  const size_t lds = (size_t)(one ? 1 : p.nw) * p.C * p.C * sizeof(T);
+  if (std::is_same<T, __bf16>::value && (p.C == 64 || p.C == 128 || one) && lds <= 160 * 1024 && pat >= 0) {
     using Kern = void (*)(ProjParams);
-    static const Kern kerns[2][3] = {
+    static const Kern kerns[3][3] = {
         {&k_project_lds<4, kPatKV>, &k_project_lds<4, kPatTok>, &k_project_lds<4, kPatPlain>},
-        {&k_project_lds<8, kPatKV>, &k_project_lds<8, kPatTok>, &k_project_lds<8, kPatPlain>}};
-    const Kern fn = kerns[p.C == 128][pat];
+        {&k_project_lds<8, kPatKV>, &k_project_lds<8, kPatTok>, &k_project_lds<8, kPatPlain>},
+        {&k_project_lds<16, kPatKV>, &k_project_lds<16, kPatTok>, &k_project_lds<16, kPatPlain>}};
+    const Kern fn = kerns[p.C == 64 ? 0 : p.C == 128 ? 1 : 2][pat];
     int dev = 0, ncu = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
@@ -871,7 +956,9 @@ hipError_t launch_project(const ProjParams& p, hipStream_t s) {
       e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     const int64_t tiles = (int64_t)p.B * (p.Np / 32);
-    const unsigned grid = (unsigned)std::min<int64_t>(blocks_for(tiles, 8), std::max(ncu, 1));
+    // one weight per workgroup: streams in multiples of 8 (one XCD each)
+    const unsigned grid = one ? (unsigned)(std::min<int64_t>((blocks_for(tiles, 8) + 7) / 8 * 8, std::max(ncu / p.nw / 8 * 8, 8)) * p.nw)
+                              : (unsigned)std::min<int64_t>(blocks_for(tiles, 8), std::max(ncu, 1));
     hipLaunchKernelGGL(fn, dim3(grid), dim3(512), lds, s, p);
     return hipGetLastError();
   }
