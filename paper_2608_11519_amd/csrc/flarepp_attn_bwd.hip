@@ -34,7 +34,7 @@
 // vector pipe, which is busy 0.6 of the time; the rest is the barrier of a
 // step (the older wave of a SIMD runs ahead and waits for the younger) and the
 // sum over the route groups.  At N = 2^20, C = 128, H = 8, M = 512: decode
-// 1.15 ms, encodes 1.36 and 1.49 ms (the second adds to a gradient), against
+// 1.15 ms, encodes 1.22 and 1.26 ms (the second adds to a gradient), against
 // 3.29, 2.46 and 2.47 ms for the kernel that kept the positions in registers
 // and walked the routes (it read every route operand per tile, added into a
 // per-wave LDS slot per tile and needed two and four route windows there).
@@ -176,6 +176,12 @@ __global__ __launch_bounds__(512) void k_attn_bwd_rs(AttnBwdRsParams p) {
         if (o + lane < SP) lds_copy16(src + min(n0 + o + lane, (int64_t)p.N - 1) * 16, dst + 4 * SP * D + 16 * o);
     }
   };
+  // The younger wave of a SIMD (w + 4), which sums the partials after its tiles
+  // (below), goes first: by age the other one does and then waits for it at
+  // the barrier.  Encode at D = 16 only (N = 2^20, M = 512: 1.37 -> 1.22 and
+  // 1.48 -> 1.26 ms); the decode sums half as much and does not gain, D = 32
+  // has one tile per barrier and loses 2%.
+  if (D == 16 && !DEC && RW > 1 && wave >= 4) __builtin_amdgcn_s_setprio(1);
   if (nsteps > 0) stage_issue(0);
 
   // ---- route side, resident ----
