@@ -790,18 +790,42 @@ __global__ __launch_bounds__(256, 1) void k_attn_bwd(AttnBwdParams p) {
 // ---------------------------------------------------------------------------
 // reductions and operand preparation
 // ---------------------------------------------------------------------------
+// Four values per thread; 32 threads cover 128 consecutive values of one o
+// (or of several: the values of all o are consecutive in the output), and the
+// eight groups of a workgroup each sum a run of the partials in order, then
+// the runs are added in order (one thread per value walked all of them: a
+// serial chain of R loads).
 __global__ __launch_bounds__(256) void k_bwd_reduce(BwdReduceParams p) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t n = (int64_t)p.O * p.M * p.D;
-  if (i >= n) return;
-  const int o = (int)(i / ((int64_t)p.M * p.D)), md = (int)(i % ((int64_t)p.M * p.D));
-  float s = p.base ? p.base[i] : 0.f;
+  __shared__ f32x4 red[8][32];
+  const int c = threadIdx.x & 31, k = threadIdx.x >> 5;
+  const int64_t i = ((int64_t)blockIdx.x * 32 + c) * 4, n = (int64_t)p.O * p.M * p.D;
+  const bool ok = i < n;
+  const int o = ok ? (int)(i / ((int64_t)p.M * p.D)) : 0, md = ok ? (int)(i % ((int64_t)p.M * p.D)) : 0;
   const int64_t st = (int64_t)p.Mp * p.D;
-  for (int q = 0; q < p.P; ++q) {
-    s = sum_run(s, p.part0 + (((int64_t)q * p.O + o) * p.R0) * st + md, st, p.R0);
-    if (p.part1) s = sum_run(s, p.part1 + (((int64_t)q * p.O + o) * p.R1) * st + md, st, p.R1);
+  // partial j of P (R0 + R1): batch entry j / (R0 + R1), then part0's chunks, then part1's
+  const int R = p.R0 + p.R1, L = p.P * R, run = (L + 7) / 8, j1 = min(L, (k + 1) * run);
+  auto at = [&](int j) __attribute__((always_inline)) {
+    const int q = j / R, r = j % R;
+    const int64_t b = (int64_t)q * p.O + o;
+    return r < p.R0 ? p.part0 + (b * p.R0 + r) * st + md : p.part1 + (b * p.R1 + r - p.R0) * st + md;
+  };
+  f32x4 s = {0.f, 0.f, 0.f, 0.f};
+  int j = k * run;
+  for (; j + 4 <= j1; j += 4) {
+    f32x4 v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = *reinterpret_cast<const f32x4*>(at(j + u));
+#pragma unroll
+    for (int u = 0; u < 4; ++u) s += v[u];
   }
-  p.out[i] = s;
+  for (; j < j1; ++j) s += *reinterpret_cast<const f32x4*>(at(j));
+  red[k][c] = s;
+  __syncthreads();
+  if (k == 0 && ok) {
+#pragma unroll
+    for (int u = 1; u < 8; ++u) s += red[u][c];
+    *reinterpret_cast<f32x4*>(p.out + i) = s;
+  }
 }
 
 // Source value src[o][m][d] of a prep job (m < M).
@@ -927,7 +951,7 @@ hipError_t launch_attn_bwd(const AttnBwdParams& p, int D, bool dec, hipStream_t 
 
 hipError_t launch_bwd_reduce(const BwdReduceParams& p, hipStream_t s) {
   const int64_t n = (int64_t)p.O * p.M * p.D;
-  k_bwd_reduce<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(p);
+  k_bwd_reduce<<<(unsigned)((n + 127) / 128), 256, 0, s>>>(p);
   return hipGetLastError();
 }
 

@@ -16,7 +16,8 @@ struct WeightFragParams {
 };
 
 struct RoutePrepParams {
-  const void* src;       // [B?][H][M][D]
+  const void* src;       // [B?][H][M][D] (q_op)
+  const void* z_src;     // the same (z_op)
   int64_t src_bstride;   // elements between batch entries (0: shared)
   int B, H, M, Mp, D;
   float qscale;
@@ -337,13 +338,13 @@ hipError_t launch_rows_sum(const RowsSumParams&, int C, hipStream_t);
 int attn_bwd_waves(int D, int nsb, int Mp, bool dec, int elem_bytes);
 size_t attn_bwd_lds_bytes(int D, int nsb, int Mp, bool dec, int waves, int elem_bytes);
 
-// Fixed-order sums of backward partials: out[o][m][d] = base[o][m][d] +
+// Fixed-order sums of backward partials: out[o][m][d] =
 // sum_{p < P} (sum_{r < R0} part0[p][o][r][m][d] + sum_{r < R1} part1[p][o][r][m][d]),
-// partials laid out [P][O][R][Mp][D] fp32 (part1 and base optional).
+// partials laid out [P][O][R][Mp][D] fp32 (part1 and R1 zero: none).
 struct BwdReduceParams {
   const float* part0; int R0;
   const float* part1; int R1;
-  const float* base; float* out;
+  float* out;
   int P, O, M, Mp, D;
 };
 // Short-side operands of a backward call from rows src[O][M][D] (fp32 or T),

@@ -55,10 +55,10 @@ __global__ void k_weight_frags(WeightFragParams p) {
 }
 
 // ---------------------------------------------------------------------------
-// Route-side operands from an fp32 (or storage-type) [B?][H][M][D] tensor:
+// Route-side operands from fp32 (or storage-type) [B?][H][M][D] tensors:
 //   q_op [B][H][Mp][D]  = src * qscale  (query operand of the encode calls and
 //                                        key operand of the decode call)
-//   z_op [B][H][D][Mp]  = src           (value operand of the decode call)
+//   z_op [B][H][D][Mp]  = z_src         (value operand of the decode call)
 // Rows M..Mp-1 are zero.
 // ---------------------------------------------------------------------------
 template <typename Ts, typename T>
@@ -70,27 +70,42 @@ __global__ void k_route_prep(RoutePrepParams p) {
   const int m = (int)((idx / p.D) % p.Mp);
   const int64_t bh = idx / ((int64_t)p.D * p.Mp);
   const int b = (int)(bh / p.H), h = (int)(bh % p.H);
-  float v = 0.f;
-  if (m < p.M) v = to_f32(((const Ts*)p.src)[b * p.src_bstride + ((int64_t)h * p.M + m) * p.D + d]);
-  if (p.q_op) ((T*)p.q_op)[(bh * p.Mp + m) * p.D + d] = from_f32<T>(v * p.qscale);
-  if (p.z_op) ((T*)p.z_op)[(bh * p.D + d) * p.Mp + m] = from_f32<T>(v);
+  const int64_t o = b * p.src_bstride + ((int64_t)h * p.M + m) * p.D + d;
+  if (p.q_op) ((T*)p.q_op)[(bh * p.Mp + m) * p.D + d] = from_f32<T>(m < p.M ? to_f32(((const Ts*)p.src)[o]) * p.qscale : 0.f);
+  if (p.z_op) ((T*)p.z_op)[(bh * p.D + d) * p.Mp + m] = from_f32<T>(m < p.M ? to_f32(((const Ts*)p.z_src)[o]) : 0.f);
 }
 
 // ---------------------------------------------------------------------------
 // Token-side values [B][H][N][D] -> d-major [B][H][D][Np], zero padded.
 // ---------------------------------------------------------------------------
-template <typename T>
-__global__ void k_dmajor(DmajorParams p) {
-  const int64_t total = (int64_t)p.BH * p.D * p.Np;
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= total) return;
-  const int n = (int)(idx % p.Np);
-  const int64_t bhd = idx / p.Np;
-  const int d = (int)(bhd % p.D);
-  const int64_t bh = bhd / p.D;
-  T v = from_f32<T>(0.f);
-  if (n < p.N) v = ((const T*)p.src)[(bh * p.N + n) * p.D + d];
-  ((T*)p.dst)[idx] = v;
+// A workgroup transposes 128 tokens of one head through LDS: whole rows in,
+// runs of tokens out (the element-wise form read one element of a row per
+// lane: 12.7 us at 9 x 9,973 x 32 in bf16, this one 6.4).
+template <typename T, int D>
+__global__ __launch_bounds__(256) void k_dmajor(DmajorParams p) {
+  using F = typename Frag<T>::type;
+  constexpr int TOK = 128, PITCH = D + 16 / (int)sizeof(T);
+  __shared__ __attribute__((aligned(16))) T tile[TOK * PITCH];
+  const int blocks = (p.Np + TOK - 1) / TOK;
+  const int64_t bh = blockIdx.x / blocks;
+  const int n0 = blockIdx.x % blocks * TOK;
+  const T* src = (const T*)p.src + bh * p.N * D;
+#pragma unroll
+  for (int e = threadIdx.x; e < TOK * D / 8; e += 256) {
+    const int n = e / (D / 8), d = 8 * (e % (D / 8));
+    *reinterpret_cast<F*>(tile + n * PITCH + d) = n0 + n < p.N ? load_frag(src + (int64_t)(n0 + n) * D + d) : zero_frag<T>();
+  }
+  __syncthreads();
+  T* dst = (T*)p.dst + bh * D * p.Np;
+#pragma unroll
+  for (int e = threadIdx.x; e < D * TOK / 8; e += 256) {
+    const int d = e / (TOK / 8), n = 8 * (e % (TOK / 8));
+    if (n0 + n >= p.Np) continue;  // Np is a multiple of 32
+    F f;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) f[j] = tile[(n + j) * PITCH + d];
+    *reinterpret_cast<F*>(dst + (int64_t)d * p.Np + n0 + n) = f;
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -883,8 +898,10 @@ hipError_t launch_route_prep(const RoutePrepParams& p, hipStream_t s) {
 
 template <typename T>
 hipError_t launch_dmajor(const DmajorParams& p, hipStream_t s) {
-  const int64_t n = (int64_t)p.BH * p.D * p.Np;
-  k_dmajor<T><<<blocks_for(n, 256), 256, 0, s>>>(p);
+  const unsigned n = (unsigned)(p.BH * ((p.Np + 127) / 128));
+  if (p.D == 16) k_dmajor<T, 16><<<n, 256, 0, s>>>(p);
+  else if (p.D == 32) k_dmajor<T, 32><<<n, 256, 0, s>>>(p);
+  else k_dmajor<T, 64><<<n, 256, 0, s>>>(p);
   return hipGetLastError();
 }
 
