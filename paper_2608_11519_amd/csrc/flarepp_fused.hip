@@ -108,10 +108,10 @@ __device__ __forceinline__ typename Frag<T>::type prep_load(const PrepFusedParam
     const int lane = (int)(si & 63), js = (int)((si >> 6) % DS);
     const int qb = (int)((si >> 6) / DS % QB), h = (int)((si >> 6) / DS / QB);
     const int g = lane >> 5, m = 32 * qb + (lane & 31);
+    if (m < p.M) {
+      v = load_frag((const T*)p.seeds + ((int64_t)h * p.M + m) * p.D + 16 * js + 8 * g);
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const float x = m < p.M ? to_f32(((const T*)p.seeds)[((int64_t)h * p.M + m) * p.D + 16 * js + 8 * g + j]) : 0.f;
-      v[j] = from_f32<T>(x * p.qscale);
+      for (int j = 0; j < 8; ++j) v[j] = from_f32<T>(to_f32(v[j]) * p.qscale);
     }
   }
   return v;
@@ -145,15 +145,28 @@ __device__ __forceinline__ void prep_store(const PrepFusedParams& p, int64_t idx
     // max over routes 4i .. 4i+3 of |scaled q|^2 of the rounded operand
     const int64_t per = (int64_t)p.H * (p.Mp / 4);
     const int h = (int)(idx % per / (p.Mp / 4)), i = (int)(idx % (p.Mp / 4));
-    float n2 = 0.f;
-    for (int m = 4 * i; m < min(4 * i + 4, p.M); ++m) {
-      float s = 0.f;
-      for (int d = 0; d < p.D; ++d) {
-        const float q = to_f32(from_f32<T>(to_f32(((const T*)p.seeds)[((int64_t)h * p.M + m) * p.D + d]) * p.qscale));
-        s = __builtin_fmaf(q, q, s);
-      }
-      n2 = fmaxf(n2, s);
+    // (16 channels of the 4 rows at a time, loaded together; past M, row M - 1)
+    const T* rows = (const T*)p.seeds + (int64_t)h * p.M * p.D;
+    float s[4] = {0.f, 0.f, 0.f, 0.f};
+    for (int d = 0; d < p.D; d += 16) {
+      typename Frag<T>::type f[4][2];
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int k = 0; k < 2; ++k) f[u][k] = load_frag(rows + (int64_t)min(4 * i + u, p.M - 1) * p.D + d + 8 * k);
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+#pragma unroll
+          for (int j = 0; j < 8; ++j) {
+            const float q = to_f32(from_f32<T>(to_f32(f[u][k][j]) * p.qscale));
+            s[u] = __builtin_fmaf(q, q, s[u]);
+          }
     }
+    float n2 = 0.f;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) n2 = 4 * i + u < p.M ? fmaxf(n2, s[u]) : n2;
     p.qnorm2[idx] = n2;
   }
 }
@@ -731,30 +744,21 @@ __global__ __launch_bounds__(64 * W) void k_encode_fused(EncFusedParams p) {
 
 // ---------------------------------------------------------------------------
 // Exact merge of split-key partials, parallel over chunk slices.  A block of
-// 256 threads owns 16 rows; thread (row, rs) folds chunks rs, rs+16, ... in
-// order, then the 16 slices of a row are folded pairwise (xor 1, 2, 4, 8);
-// every slice then holds the whole row (equal up to the rounding order of its
-// folds), and output element d is taken from slice d % 16.  Each thread issues the loads of kCombineBatch partials before folding any
-// of them, so a batch costs one memory round trip.
+// 256 threads owns 16 rows; 16 lanes share a row, as D / 4 runs of 4 channels
+// times 64 / D chunk slices (slice rg folds chunks rg, rg + 64 / D, ... in
+// order, kCombineBatch of them at a time: one memory round trip, one rescale
+// by the batch's maximum), then a row's slices are folded pairwise.  A slice
+// reads whole rows of neighbouring lanes, and only 4 channels per lane are
+// exchanged (a thread that held all D of a row spent 4 folds of D + 2 lane
+// exchanges; 16 chunks: 6.3 and 5.2 us at 4 x 16,384 x 128, now 5.8 and 4.7; D = 32 at
+// 2 x 50,000 x 256: 9.1 and 7.4, now 6.8 and 5.1).
 // ---------------------------------------------------------------------------
-constexpr int kCombineBatch = 4;
-
-template <int D>
-__device__ __forceinline__ void fold_partial(float& m, float& l, float (&a)[D], float mr, float lr,
-                                             const float (&ar)[D]) {
-  if (mr == -INFINITY) return;  // empty chunk: (-inf, 0, 0)
-  const float mn = fmaxf(m, mr);
-  const float wa = __builtin_amdgcn_exp2f(m - mn), wb = __builtin_amdgcn_exp2f(mr - mn);
-  l = l * wa + lr * wb;
-#pragma unroll
-  for (int d = 0; d < D; ++d) a[d] = a[d] * wa + ar[d] * wb;
-  m = mn;
-}
+constexpr int kCombineBatch = 8;
 
 template <typename T, int D>
 __global__ __launch_bounds__(256) void k_combine_par(CombineParams p) {
-  constexpr int KS = D / 16;
-  const int t = threadIdx.x, rs = t & 15;
+  constexpr int KS = D / 16, DQ = D / 4, RG = 16 / DQ;
+  const int t = threadIdx.x, d = 4 * (t % DQ), rg = t / DQ % RG;
   // this thread's first preparation item: loads now, store at the end
   const int64_t pi0 = (int64_t)threadIdx.x * gridDim.x + blockIdx.x;
   typename Frag<T>::type pv;
@@ -762,85 +766,92 @@ __global__ __launch_bounds__(256) void k_combine_par(CombineParams p) {
   const int rows_per_bh = p.Mp / 16;
   const int64_t bh = blockIdx.x / rows_per_bh;
   const int qrow = (blockIdx.x % rows_per_bh) * 16 + (t >> 4);
-  float m = -INFINITY, l = 0.f, a[D];
-#pragma unroll
-  for (int d = 0; d < D; ++d) a[d] = 0.f;
-  for (int r0 = rs; r0 < p.R; r0 += 16 * kCombineBatch) {
-    float mr[kCombineBatch], lr[kCombineBatch], ar[kCombineBatch][D];
+  float m = -INFINITY, l = 0.f;
+  f32x4 a = {0.f, 0.f, 0.f, 0.f};
+  // an empty chunk is (-inf, 0, 0): weight 0, whatever the maximum
+  auto weight = [](float mr, float mn) __attribute__((always_inline)) {
+    return mr == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mr - mn);
+  };
+  for (int r0 = rg; r0 < p.R; r0 += RG * kCombineBatch) {
+    f32x2 ml[kCombineBatch];
+    f32x4 ar[kCombineBatch];
 #pragma unroll
     for (int u = 0; u < kCombineBatch; ++u) {
-      const int r = r0 + 16 * u;
-      mr[u] = -INFINITY;
-      lr[u] = 0.f;
+      const int r = r0 + RG * u;
+      const int64_t pidx = (bh * p.R + min(r, p.R - 1)) * p.Mp + qrow;
+      ml[u] = *reinterpret_cast<const f32x2*>(p.part_ml + pidx * 2);
+      ar[u] = *reinterpret_cast<const f32x4*>(p.part_acc + pidx * D + d);
+      if (r >= p.R) ml[u][0] = -INFINITY;
+    }
+    float mn = m;
 #pragma unroll
-      for (int d = 0; d < D; ++d) ar[u][d] = 0.f;
-      if (r < p.R) {
-        const int64_t pidx = (bh * p.R + r) * p.Mp + qrow;
-        const f32x2 ml = *reinterpret_cast<const f32x2*>(p.part_ml + pidx * 2);
-        mr[u] = ml[0];
-        lr[u] = ml[1];
+    for (int u = 0; u < kCombineBatch; ++u) mn = fmaxf(mn, ml[u][0]);
+    const float w0 = weight(m, mn);
+    l *= w0;
+    a *= w0;
 #pragma unroll
-        for (int d = 0; d < D; d += 4) {
-          const f32x4 v = *reinterpret_cast<const f32x4*>(p.part_acc + pidx * D + d);
-          ar[u][d] = v[0]; ar[u][d + 1] = v[1]; ar[u][d + 2] = v[2]; ar[u][d + 3] = v[3];
-        }
+    for (int u = 0; u < kCombineBatch; ++u) {
+      const float w = weight(ml[u][0], mn);
+      if (w != 0.f) {  // (an unread or empty partial may hold anything)
+        l += ml[u][1] * w;
+        a += ar[u] * w;
       }
     }
-#pragma unroll
-    for (int u = 0; u < kCombineBatch; ++u) fold_partial<D>(m, l, a, mr[u], lr[u], ar[u]);
+    m = mn;
   }
 #pragma unroll
-  for (int k = 1; k < 16; k <<= 1) {
-    float ao[D];
+  for (int k = DQ; k < 16; k <<= 1) {
+    f32x4 ao;
 #pragma unroll
-    for (int d = 0; d < D; ++d) ao[d] = __shfl_xor(a[d], k, 64);
+    for (int j = 0; j < 4; ++j) ao[j] = __shfl_xor(a[j], k, 64);
     const float mo = __shfl_xor(m, k, 64), lo = __shfl_xor(l, k, 64);
-    fold_partial<D>(m, l, a, mo, lo, ao);
+    const float mn = fmaxf(m, mo), wa = weight(m, mn), wb = weight(mo, mn);
+    l = l * wa + lo * wb;
+    a = a * wa + ao * wb;
+    m = mn;
   }
   const bool valid = qrow < p.M;
   const float inv = (valid && l > 0.f) ? 1.f / l : 0.f;
   const int qb = qrow >> 5, qc = qrow & 31;
+  const f32x4 out = a * inv;
   if (p.frag && p.q_op && p.qnorm2) {
     // max over the wave's 4 rows of |scaled q|^2 (of the rounded operand),
     // one entry per wave
     float n2 = 0.f;
     if (valid) {
 #pragma unroll
-      for (int d = 0; d < D; ++d) {
-        const float q = to_f32(from_f32<T>(a[d] * inv * p.qscale));
+      for (int j = 0; j < 4; ++j) {
+        const float q = to_f32(from_f32<T>(out[j] * p.qscale));
         n2 = __builtin_fmaf(q, q, n2);
       }
     }
+#pragma unroll
+    for (int k = 1; k < DQ; k <<= 1) n2 += __shfl_xor(n2, k, 64);
     n2 = fmaxf(n2, __shfl_xor(n2, 16, 64));
     n2 = fmaxf(n2, __shfl_xor(n2, 32, 64));
     if ((t & 63) == 0) p.qnorm2[bh * (p.Mp / 4) + (blockIdx.x % rows_per_bh) * 4 + (t >> 6)] = n2;
   }
+  if (rg == 0) {
+    const float q = p.qscale;
+    if (valid && p.out32) store4(p.out32 + (bh * p.M + qrow) * D + d, out[0], out[1], out[2], out[3]);
+    if (p.q_op) {  // rows, or q fragment order
+      const int64_t off = p.frag ? (int64_t)bh * p.Mp * D + ((int64_t)(qb * KS + (d >> 4)) * 64 + ((d >> 3) & 1) * 32 + qc) * 8 + (d & 7)
+                                 : (bh * p.Mp + qrow) * D + d;
+      store4((T*)p.q_op + off, out[0] * q, out[1] * q, out[2] * q, out[3] * q);
+    }
+    if (p.z_op) {
+      if (!p.frag) {
 #pragma unroll
-  for (int d0 = 0; d0 < D; d0 += 16) {
-    const int d = d0 + rs;
-    float v = 0.f;
-#pragma unroll
-    for (int k = 0; k < D; ++k)
-      if (k == d) v = a[k];
-    const float out = v * inv;
-    if (valid && p.out32) p.out32[(bh * p.M + qrow) * D + d] = out;
-    if (!p.frag) {
-      if (p.q_op) ((T*)p.q_op)[(bh * p.Mp + qrow) * D + d] = from_f32<T>(out * p.qscale);
-      if (p.z_op) ((T*)p.z_op)[(bh * D + d) * p.Mp + qrow] = from_f32<T>(out);
-    } else {
-      if (p.q_op) {  // q fragment order
-        const int js = d >> 4, gq = (d >> 3) & 1, jj = d & 7;
-        const int64_t off = (int64_t)bh * p.Mp * D + ((int64_t)(qb * KS + js) * 64 + gq * 32 + qc) * 8 + jj;
-        ((T*)p.q_op)[off] = from_f32<T>(out * p.qscale);
-      }
-      if (p.z_op) {  // z fragment order; row qc of route tile qb
+        for (int j = 0; j < 4; ++j) ((T*)p.z_op)[(bh * D + d + j) * p.Mp + qrow] = from_f32<T>(out[j]);
+      } else {  // z fragment order; row qc of route tile qb
         const int hf = qc >> 4, rr = qc & 15, gz = (rr >> 2) & 1, jj = 4 * (rr >> 3) + (rr & 3);
         T* z = (T*)p.z_op + bh * z_frag_elems_per_head(p.Mp, D);
-        z[z_frag_index(qb, hf, d >> 5, gz, d & 31, jj, D)] = from_f32<T>(out);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) z[z_frag_index(qb, hf, (d + j) >> 5, gz, (d + j) & 31, jj, D)] = from_f32<T>(out[j]);
       }
     }
+    if (valid && p.lse && d == 0) p.lse[bh * p.M + qrow] = 0.6931471805599453f * (m + __log2f(l));
   }
-  if (valid && p.lse && rs == 0) p.lse[bh * p.M + qrow] = 0.6931471805599453f * (m + __log2f(l));
   if (pi0 < p.prep_n) prep_store<T>(p.prep, pi0, pv);
   for (int64_t k = 1;; ++k) {  // further items (when there are more than threads)
     const int64_t i = (k * blockDim.x + threadIdx.x) * gridDim.x + blockIdx.x;
