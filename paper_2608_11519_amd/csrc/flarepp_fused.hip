@@ -1263,7 +1263,7 @@ __global__ __launch_bounds__(64 * dec_waves(16 * KSC)) void k_decode2(DecFusedPa
   constexpr bool ONES_ROW = (D == 16);
   constexpr int C = KSC * 16, CB = C / 32, HG = CB / GB;
   constexpr int WELEMS = GB * KSC * kFrag, WOE = CB * KPG * kFrag;
-  constexpr int NW = dec_waves(C), TOK = 32 * NW;
+  const int TOK = 32 * (RES ? p.waves : dec_waves(C));
   constexpr int ZC = D < 32 ? D : 32;  // value rows per z fragment
   static_assert(C <= 128, "per-group merge accumulators are sized for C <= 128");
   extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -1289,6 +1289,7 @@ __global__ __launch_bounds__(64 * dec_waves(16 * KSC)) void k_decode2(DecFusedPa
   for (int ks = 0; ks < KSC; ++ks)
     xf[ks] = load_frag((const T*)p.x + ((int64_t)b * p.N + min(xrow, p.N - 1)) * C + 16 * ks + 8 * g);
   lds_wait_barrier();
+  if (RES && wave >= p.waves) return;  // it only helped with the copies (no barrier follows)
 
   // z operand lanes: value-row lanes walk the head's z fragments; on D = 16
   // the lanes of rows 16 .. 31 read the constant block
@@ -1478,7 +1479,7 @@ __global__ __launch_bounds__(64 * dec_waves(16 * KSC)) void k_decode3(DecFusedPa
   constexpr bool ONES_ROW = (D == 16);
   constexpr int C = KSC * 16, CB = C / 32, HG = CB / GB;
   constexpr int WELEMS = GB * KSC * kFrag, WOE = CB * KPG * kFrag;
-  constexpr int NW = dec_waves(C), TOK = 32 * NW;
+  const int TOK = 32 * p.waves;
   constexpr int ZC = D < 32 ? D : 32;
   constexpr int NT = RT * HPG;      // route tiles per group
   constexpr int NP = GB * KSC;      // projection MFMAs per group
@@ -1506,6 +1507,7 @@ __global__ __launch_bounds__(64 * dec_waves(16 * KSC)) void k_decode3(DecFusedPa
   for (int s0 = 0; s0 < HG; ++s0) dec2_stage_issue<T, D, KSC>(p, smem + s0 * SB, b, s0);
   if (ONES_ROW && threadIdx.x < 2) store_frag<T>(cst + 8 * threadIdx.x, threadIdx.x == 0 ? fill_frag<T>(1.f) : zero_frag<T>());
   lds_wait_barrier();
+  if (wave >= p.waves) return;  // it only helped with the copies (no barrier follows)
 
   const bool konst = ONES_ROW && c >= 16;
   const uint32_t zstep = konst ? 0u : (uint32_t)(2 * ZC * 8 * sizeof(T));
@@ -2077,13 +2079,28 @@ hipError_t launch_combine_par(const CombineParams& p, hipStream_t s) {
   return hipGetLastError();
 }
 
+// Waves of a resident decode's workgroup that own tokens (32 each); the others
+// help with the stage copies and end.  With few tokens a workgroup of eight
+// tiles keeps two waves on each SIMD of a few CUs while the others idle: the
+// fewest waves with which the workgroups still fit the 256 CUs in one round
+// (1,554 tokens of 128 channels, M = 64: 14.4 us with eight, 11.8 with one; 1,024
+// of 64 in fp32, M = 32: 20.1 and 13.6).  The tiles and their results are the
+// same.
+static int dec_active_waves(const DecFusedParams& p) {
+  int w = 8;
+  while (w > 1 && (int64_t)p.B * ((p.N + 16 * w - 1) / (16 * w)) <= 256) w /= 2;
+  return w;
+}
+
 template <typename T, int D, int KSC>
-static hipError_t dec_launch(const DecFusedParams& p, hipStream_t s) {
+static hipError_t dec_launch(const DecFusedParams& pp, hipStream_t s) {
   if constexpr (!dec_fused_ok(sizeof(T), D, KSC) || !fused_width_ok(16 * KSC, sizeof(T))) {
     return hipErrorInvalidValue;
   } else {
     constexpr int NW = dec_waves(16 * KSC);
-    const unsigned grid = (unsigned)((int64_t)p.B * ((p.N + 32 * NW - 1) / (32 * NW)));
+    DecFusedParams p = pp;
+    p.waves = p.kind == kDecodeGroupsResident ? dec_active_waves(p) : NW;
+    const unsigned grid = (unsigned)((int64_t)p.B * ((p.N + 32 * p.waves - 1) / (32 * p.waves)));
     if constexpr (sizeof(T) == 2 && (D == 16 || D == 32) && KSC <= 8) {
       if (p.kind == kDecodePersist) {  // one persistent workgroup per CU, static LDS
         if (persist_lds_bytes(16 * KSC, D, p.Mp, sizeof(T)) > kPersistLdsBytes ||

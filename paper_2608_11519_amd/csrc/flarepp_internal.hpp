@@ -172,6 +172,7 @@ struct DecFusedParams {
   int stage_elems;    // elements per LDS stage buffer (k_decode_fused)
   int stage_bytes;    // bytes per head-group stage (k_decode2)
   int kind;           // DecodeKind
+  int waves;          // set by the launcher: waves of a workgroup that own tokens
 };
 
 // Fused path coverage.  bf16: C in {64, 128, 256}; fp32 (a correctness path):
