@@ -736,7 +736,7 @@ BwdWs bwd_ws(void* base, int dtype, int64_t B, int64_t N, int64_t C, int64_t H, 
   w.pq = (float*)cv.take(f4 * BH * R * Mp * D);
   if (gg) {
     w.wg_prob = bwd_lo_parts(dtype) ? 7 : 5;
-    w.splits = flarepp::wgrad_chunks(T, (int)C, w.wg_prob, &w.wg_chunk);
+    w.splits = flarepp::wgrad_chunks(T, w.wg_prob, &w.wg_chunk);
     w.gpart = (float*)cv.take(f4 * w.wg_prob * w.splits * C * C);
   } else {
     w.splits = gemm_splits(T, C, &w.kchunk);

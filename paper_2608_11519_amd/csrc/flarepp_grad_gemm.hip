@@ -9,13 +9,11 @@
 //   as their k index, come out of the row-major tiles through transposing LDS
 //   reads, with no register staging or repacking between.  2^20 x 128: 502 us
 //   for nine arrays of 268 MB, X read by six problems (796 us with operand
-//   tiles staged through registers); 100,000 x 256: 164 us (305).
-// * k_rows_sum: dX = sum_j G_j W_j^T over the four projections, persistent
-//   workgroups with the weights resident in LDS; a wave holds a tile's rows of
-//   one projection in registers while the next one's are loaded.  2^20 x 128:
-//   300 us for 1.6 GB (5.4 TB/s; 413 us as a tiled GEMM); 100,000 x 256: 138 us
-//   (172), where four workgroups each read the rows for a quarter of the
-//   columns.
+//   tiles staged through registers); 100,000 x 256: 115 us (305; 164 with half
+//   of the rows per workgroup, which read B twice).
+// * k_rows_sum, k_rows_sum_stream: dX = sum_j G_j W_j^T over the four
+//   projections by persistent workgroups.  2^20 x 128: 300 us for 1.6 GB (5.4
+//   TB/s; 413 us as a tiled GEMM); 100,000 x 256: 89 us (172).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -31,17 +29,17 @@ using T = __bf16;
 // ---------------------------------------------------------------------------
 // weight gradients
 // ---------------------------------------------------------------------------
-// Workgroup tile TI x TO of C x C; steps of 32 tokens in a ring of NBUF LDS
-// buffers ([32][TI] of A, then [32][TO] of B).  Eight waves as 4 x 2 tiles of
-// 32 x TO / 2 (C = 64: 2 x 2 tiles of 32 x 32, twice: each half of the waves
-// takes one half of a step's tokens).
+// A workgroup computes the whole C x C product of its tokens; steps of 32
+// tokens in a ring of NBUF LDS buffers ([32][C] of A, then of B).  Eight waves
+// as 4 x 2 tiles of C / 4 x C / 2 (C = 64: 2 x 2 tiles of 32 x 32, twice: each
+// half of the waves takes one half of a step's tokens).
 template <int C> struct Wgrad {
-  static constexpr int TI = C < 128 ? 64 : 128, TO = C;
+  static constexpr int TI = C, TO = C;
   static constexpr int KG = C == 64 ? 2 : 1;              // groups of waves over a step's tokens
-  static constexpr int WO = 2, WI = TI / 32;              // waves along o, i of one group
-  static constexpr int NB = TO / WO / 32;                 // 32 x 32 blocks of a wave
+  static constexpr int WO = 2, WI = C == 64 ? 2 : 4;      // waves along o, i of one group
+  static constexpr int NI = TI / WI / 32, NB = TO / WO / 32;  // 32 x 32 blocks of a wave
   static constexpr int BUF = 32 * (TI + TO) * 2;          // bytes of a step
-  static constexpr int NBUF = C == 64 ? 12 : C == 128 ? 8 : 5;
+  static constexpr int NBUF = C == 64 ? 12 : C == 128 ? 8 : 4;
   static constexpr int IPW = BUF / 1024 / 8;              // 1 KiB copies of a step per wave
   static_assert(WI * WO * KG == 8 && BUF % 8192 == 0 && BUF * NBUF <= 160 * 1024, "layout");
 };
@@ -57,20 +55,17 @@ __device__ __forceinline__ int wg_slot(int row, int s) {
 template <int C>
 __global__ __launch_bounds__(512) void k_wgrad(WgradParams p) {
   using W = Wgrad<C>;
-  constexpr int TI = W::TI, TO = W::TO, NB = W::NB;
+  constexpr int TI = W::TI, TO = W::TO, NI = W::NI, NB = W::NB;
   __shared__ __attribute__((aligned(16))) char smem[W::BUF * W::NBUF];
   const int lane = lane_id(), g = lane >> 5, c = lane & 31, r4 = lane >> 4, i16 = lane & 15, wave = wave_id();
   // the problems of one token chunk run on one XCD (workgroups are dealt to
   // the 8 XCDs in turn), so X, which most of them read, comes from its L2
   // after the first read
-  constexpr int HALVES = C / TI;
-  const int per = p.nprob * HALVES;
-  const int L = blockIdx.x, rr = L >> 3, sub = rr % per, chunk = rr / per * 8 + (L & 7);
+  const int L = blockIdx.x, rr = L >> 3, prob = rr % p.nprob, chunk = rr / p.nprob * 8 + (L & 7);
   if (chunk >= p.nchunks) return;  // whole workgroup, before any barrier
-  const int prob = sub / HALVES, i0 = sub % HALVES * TI;
   const int64_t t0 = (int64_t)chunk * p.chunk, t1 = min(p.T, t0 + p.chunk);
   const int nsteps = (int)((t1 - t0 + 31) / 32);
-  const T* A = static_cast<const T*>(p.a[prob]) + i0;
+  const T* A = static_cast<const T*>(p.a[prob]);
   const T* B = static_cast<const T*>(p.b[prob]);
 
   // copies of step s: this wave's IPW KiB of the step's buffer (rows past the
@@ -99,15 +94,18 @@ __global__ __launch_bounds__(512) void k_wgrad(WgradParams p) {
     const int s = 4 * f + 2 * (r4 & 1) + ((i16 & 3) >> 1);
     return row * cols * 2 + (cols == TO ? wg_slot<TO>(row, s) : wg_slot<TI>(row, s)) * 16 + 8 * (i16 & 1);
   };
-  const int aoff = frag_off(TI, wi);
-  int boff[NB];
+  int aoff[NI], boff[NB];
+#pragma unroll
+  for (int f = 0; f < NI; ++f) aoff[f] = frag_off(TI, wi * NI + f);
 #pragma unroll
   for (int f = 0; f < NB; ++f) boff[f] = 32 * TI * 2 + frag_off(TO, wo * NB + f);
-  f32x16 acc[NB];
+  f32x16 acc[NI][NB];
 #pragma unroll
-  for (int f = 0; f < NB; ++f)
+  for (int i = 0; i < NI; ++i)
 #pragma unroll
-    for (int e = 0; e < 16; ++e) acc[f][e] = 0.f;
+    for (int f = 0; f < NB; ++f)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[i][f][e] = 0.f;
 
   for (int s = 0; s < nsteps; ++s) {
     // step s has landed: at most the NBUF - 2 steps after it are in flight
@@ -127,16 +125,21 @@ __global__ __launch_bounds__(512) void k_wgrad(WgradParams p) {
 #pragma unroll
     for (int k = 0; k < 2 / W::KG; ++k) {
       const int ks = W::KG == 2 ? kg : k;
-      const char* ap = buf + ks * 16 * TI * 2 + aoff;
-      const bf16x8 af = lds_tr_frag(ap, ap + 8 * TI * 2);
-      bf16x8 bf[NB];
+      bf16x8 af[NI], bf[NB];
+#pragma unroll
+      for (int f = 0; f < NI; ++f) {
+        const char* ap = buf + ks * 16 * TI * 2 + aoff[f];
+        af[f] = lds_tr_frag(ap, ap + 8 * TI * 2);
+      }
 #pragma unroll
       for (int f = 0; f < NB; ++f) {
         const char* bp = buf + ks * 16 * TO * 2 + boff[f];
         bf[f] = lds_tr_frag(bp, bp + 8 * TO * 2);
       }
 #pragma unroll
-      for (int f = 0; f < NB; ++f) mma(acc[f], af, bf[f]);
+      for (int i = 0; i < NI; ++i)
+#pragma unroll
+        for (int f = 0; f < NB; ++f) mma(acc[i][f], af[i], bf[f]);
     }
   }
   if constexpr (W::KG == 2) {
@@ -145,18 +148,20 @@ __global__ __launch_bounds__(512) void k_wgrad(WgradParams p) {
     float* x = reinterpret_cast<float*>(smem) + (wi * W::WO + wo) * 1024 + lane;
     if (kg == 1) {
 #pragma unroll
-      for (int e = 0; e < 16; ++e) x[64 * e] = acc[0][e];
+      for (int e = 0; e < 16; ++e) x[64 * e] = acc[0][0][e];
     }
     __syncthreads();
     if (kg == 1) return;
 #pragma unroll
-    for (int e = 0; e < 16; ++e) acc[0][e] += x[64 * e];
+    for (int e = 0; e < 16; ++e) acc[0][0][e] += x[64 * e];
   }
-  float* out = p.part + ((int64_t)prob * p.nchunks + chunk) * C * C + (int64_t)(i0 + 32 * wi) * C + 32 * wo * NB + c;
+  float* out = p.part + ((int64_t)prob * p.nchunks + chunk) * C * C + (int64_t)(32 * wi * NI) * C + 32 * wo * NB + c;
 #pragma unroll
-  for (int f = 0; f < NB; ++f)
+  for (int i = 0; i < NI; ++i)
 #pragma unroll
-    for (int e = 0; e < 16; ++e) out[(int64_t)acc_row(lane, e) * C + 32 * f] = acc[f][e];
+    for (int f = 0; f < NB; ++f)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) out[(32 * i + acc_row(lane, e)) * C + 32 * f] = acc[i][f][e];
 }
 
 // out[o] = the sum, in order, of its problems' chunk partials; four values per
@@ -185,23 +190,19 @@ __global__ __launch_bounds__(256) void k_wgrad_sum(WgradSumParams p) {
 // ---------------------------------------------------------------------------
 // input gradient
 // ---------------------------------------------------------------------------
-// Eight waves; a wave walks tiles of 32 tokens.  NB output blocks of 32
-// columns per workgroup (C = 256: a quarter of them, the four quarters of one
-// token stream on one XCD), so the four weights' fragments fill at most 128
-// KiB of LDS.
-template <int KS, int NB>
+// C <= 128: the four weights' fragments stay in LDS (at most 128 KiB); eight
+// waves, each walking tiles of 32 tokens with a tile's rows of one projection
+// in registers while the next one's are loaded.
+template <int KS>
 __global__ __launch_bounds__(512) void k_rows_sum(RowsSumParams p) {
-  constexpr int C = 16 * KS, SL = C / 32 / NB, SEG = KS * NB * 512;  // slices, elements of a weight's slice
+  constexpr int C = 16 * KS, NB = C / 32, SEG = C * C;  // output blocks, elements of a weight
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const int lane = lane_id(), g = lane >> 5, c = lane & 31, wave = wave_id();
-  const int L = blockIdx.x, rr = L >> 3, slice = rr % SL, stream = rr / SL * 8 + (L & 7);
-  const int64_t streams = gridDim.x / SL;  // a multiple of 8
 #pragma unroll
-  for (int j = 0; j < 4; ++j)
-    copy_to_lds(static_cast<const T*>(p.wf[j]) + (int64_t)slice * SEG, smem + j * SEG * 2, SEG / 8, 512);
+  for (int j = 0; j < 4; ++j) copy_to_lds(p.wf[j], smem + j * SEG * 2, SEG / 8, 512);
   const T* wl = reinterpret_cast<const T*>(smem) + lane * 8;
-  const int64_t tiles = (p.T + 31) / 32, stride = streams * 8;
-  int64_t t = stream * 8 + wave;
+  const int64_t tiles = (p.T + 31) / 32, stride = (int64_t)gridDim.x * 8;
+  int64_t t = (int64_t)blockIdx.x * 8 + wave;
   auto load = [&](bf16x8 (&x)[KS], int64_t tile, int j) __attribute__((always_inline)) {
     const T* src = static_cast<const T*>(p.in[j]) + min(tile * 32 + c, p.T - 1) * C + 8 * g;
 #pragma unroll
@@ -241,7 +242,7 @@ __global__ __launch_bounds__(512) void k_rows_sum(RowsSumParams p) {
     seg(xa, xb, t, 2);
     seg(xb, xa, t, 3);
     // rows = tokens, columns along the lanes: 128 contiguous bytes per row
-    float* out = p.out + t * 32 * C + slice * NB * 32 + c;
+    float* out = p.out + t * 32 * C + c;
     const int left = (int)min((int64_t)32, p.T - t * 32);
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
@@ -254,24 +255,119 @@ __global__ __launch_bounds__(512) void k_rows_sum(RowsSumParams p) {
   }
 }
 
+// The same product at C = 256, where the four weights (512 KiB) do not fit in
+// LDS: the tokens' rows do the waiting there instead.  A workgroup walks tiles
+// of 64 tokens; each projection's rows [64][256] are one slot of a ring of
+// four (direct copies, up to three slots ahead), and a wave computes 32 output
+// columns for all 64 tokens with its weight fragments read from L2, which
+// holds all four weights, one projection ahead.  Every row is read once
+// (100,000 tokens: 89 us for 307 MB; a quarter of the columns per workgroup with the
+// weights in LDS read them four times: 138 us).
+__global__ __launch_bounds__(512) void k_rows_sum_stream(RowsSumParams p) {
+  constexpr int C = 256, KS = 16, TOK = 64, SLOT = TOK * C * 2, RING = 4;
+  __shared__ __attribute__((aligned(16))) char smem[RING * SLOT];
+  const int lane = lane_id(), g = lane >> 5, c = lane & 31, wave = wave_id();
+  const int64_t tiles = (p.T + TOK - 1) / TOK;
+  const int mine = (int)((tiles - blockIdx.x + gridDim.x - 1) / gridDim.x);  // this workgroup's tiles
+  const int nseg = 4 * mine;
+  // slot q of the sequence: projection q % 4 of tile q / 4; 16-byte chunk s of
+  // a row lies at chunk s ^ (row % 8), so that a column of chunks falls in
+  // different banks
+  auto issue = [&](int q) __attribute__((always_inline)) {
+    if (q >= nseg) return;
+    const T* src = static_cast<const T*>(p.in[q & 3]);
+    const int64_t t0 = (blockIdx.x + (int64_t)(q >> 2) * gridDim.x) * TOK;
+    char* dst = smem + q % RING * SLOT;
+    int ln = lane;
+    asm volatile("" : "+v"(ln));
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {  // 32 KiB, 4 copies of 1 KiB per wave (two rows each)
+      const int k = 4 * wave + u, row = 2 * k + (ln >> 5);
+      lds_copy16(src + min(t0 + row, p.T - 1) * C + 8 * ((ln & 31) ^ (row & 7)), dst + k * 1024);
+    }
+  };
+  // this wave's weight fragments of projection j (output block = wave)
+  // (the lane index is re-read in the loads and copies, so that their addresses
+  // do not stay in registers across the tiles)
+  auto weights = [&](bf16x8 (&w)[KS], int j) __attribute__((always_inline)) {
+    int ln = lane;
+    asm volatile("" : "+v"(ln));
+    const T* src = static_cast<const T*>(p.wf[j]) + (wave * KS * 64 + ln) * 8;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) w[ks] = load_frag(src + ks * 512);
+  };
+  bf16x8 wa[KS], wb[KS];
+  weights(wa, 0);
+  for (int q = 0; q < RING - 1; ++q) issue(q);
+  f32x16 acc[2];
+  auto seg = [&](int q, bf16x8 (&w)[KS], bf16x8 (&nw)[KS]) __attribute__((always_inline)) {
+    // slot q has landed: of the copies, at most those of the slots after it
+    // are in flight (the weight loads and stores between them only make the
+    // wait stricter)
+    if (q + RING - 2 < nseg) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(4 * (RING - 2)) : "memory");
+    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    lds_barrier();
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) asm volatile("; weights %0" : "+v"(w[ks]));
+    if (q + 1 < nseg) weights(nw, (q + 1) & 3);
+    asm volatile("" ::: "memory");  // the copies go out after the weight loads
+    issue(q + RING - 1);            // into the slot of step q - 1, which every wave has left
+    const char* slot = smem + q % RING * SLOT;
+    // chunk (2 ks + g) ^ (c % 8): the low three bits repeat every four k steps
+    const char* at[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) at[k] = slot + c * C * 2 + (((2 * k + g) ^ (c & 7)) << 4);
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+        mma(acc[h], load_frag(reinterpret_cast<const T*>(at[ks & 3] + (ks >> 2) * 128 + h * 32 * C * 2)), w[ks]);
+    // the LDS reads of two k steps go out ahead of the products of the step
+    // before them (all of them hoisted would not fit the registers)
+    __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
+#pragma unroll
+    for (int ks = 0; ks < KS - 2; ks += 2) {
+      __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
+      __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
+    }
+    __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
+  };
+  for (int m = 0; m < mine; ++m) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[h][e] = 0.f;
+    seg(4 * m, wa, wb);
+    seg(4 * m + 1, wb, wa);
+    seg(4 * m + 2, wa, wb);
+    seg(4 * m + 3, wb, wa);
+    const int64_t t0 = (blockIdx.x + (int64_t)m * gridDim.x) * TOK;
+    const int left = (int)min((int64_t)TOK, p.T - t0);
+    float* out = p.out + t0 * C + 32 * wave + c;
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const int row = 32 * h + acc_row(lane, e);
+        if (row < left) out[row * C] = acc[h][e];
+      }
+  }
+}
+
 template <int C>
 hipError_t wgrad_go(const WgradParams& p, hipStream_t s) {
-  const int per = p.nprob * (C / Wgrad<C>::TI);
-  k_wgrad<C><<<(unsigned)((p.nchunks + 7) / 8 * 8 * per), 512, 0, s>>>(p);
+  k_wgrad<C><<<(unsigned)((p.nchunks + 7) / 8 * 8 * p.nprob), 512, 0, s>>>(p);
   return hipGetLastError();
 }
 
-template <int KS, int NB>
+template <int KS>
 hipError_t rows_sum_go(const RowsSumParams& p, hipStream_t s) {
-  constexpr int SL = KS / 2 / NB;
-  constexpr size_t lds = (size_t)4 * KS * NB * 1024;
-  const void* fn = reinterpret_cast<const void*>(&k_rows_sum<KS, NB>);
+  constexpr size_t lds = (size_t)4 * 256 * KS * KS * 2;
+  const void* fn = reinterpret_cast<const void*>(&k_rows_sum<KS>);
   hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
-  // streams of 8 waves, a multiple of 8 (one XCD each), one workgroup per CU
-  const int64_t tiles = (p.T + 31) / 32, want = ((tiles + 7) / 8 + 7) / 8 * 8;
-  const int64_t streams = std::min<int64_t>(want, 256 / SL);
-  k_rows_sum<KS, NB><<<(unsigned)(streams * SL), 512, lds, s>>>(p);
+  const int64_t groups = ((p.T + 31) / 32 + 7) / 8;  // of eight tiles
+  k_rows_sum<KS><<<(unsigned)std::min<int64_t>(groups, 256), 512, lds, s>>>(p);
   return hipGetLastError();
 }
 
@@ -279,9 +375,8 @@ hipError_t rows_sum_go(const RowsSumParams& p, hipStream_t s) {
 
 // Chunks of tokens: one round of workgroups over the 256 CUs, a multiple of 8
 // (one XCD each) where there are that many, at least 128 tokens each.
-int wgrad_chunks(int64_t T, int C, int nprob, int64_t* chunk) {
-  const int64_t per = (int64_t)nprob * (C == 256 ? 2 : 1);
-  int64_t n = std::max<int64_t>(1, 256 / per);
+int wgrad_chunks(int64_t T, int nprob, int64_t* chunk) {
+  int64_t n = std::max<int64_t>(1, 256 / nprob);
   if (n >= 8) n = n / 8 * 8;
   n = std::min(n, (T + 127) / 128);
   *chunk = ((T + n - 1) / n + 31) / 32 * 32;
@@ -299,7 +394,11 @@ hipError_t launch_wgrad_sum(const WgradSumParams& p, hipStream_t s) {
 }
 
 hipError_t launch_rows_sum(const RowsSumParams& p, int C, hipStream_t s) {
-  return C == 64 ? rows_sum_go<4, 2>(p, s) : C == 128 ? rows_sum_go<8, 4>(p, s) : rows_sum_go<16, 2>(p, s);
+  if (C == 256) {
+    k_rows_sum_stream<<<(unsigned)std::min<int64_t>((p.T + 63) / 64, 256), 512, 0, s>>>(p);
+    return hipGetLastError();
+  }
+  return C == 64 ? rows_sum_go<4>(p, s) : rows_sum_go<8>(p, s);
 }
 
 }  // namespace flarepp

@@ -331,7 +331,7 @@ struct RowsSumParams {
   int64_t T;
 };
 constexpr bool grad_gemm_ok(int C, int elem_bytes) { return elem_bytes == 2 && (C == 64 || C == 128 || C == 256); }
-int wgrad_chunks(int64_t T, int C, int nprob, int64_t* chunk);
+int wgrad_chunks(int64_t T, int nprob, int64_t* chunk);
 hipError_t launch_wgrad(const WgradParams&, int C, hipStream_t);
 hipError_t launch_wgrad_sum(const WgradSumParams&, hipStream_t);
 hipError_t launch_rows_sum(const RowsSumParams&, int C, hipStream_t);
