@@ -925,6 +925,11 @@ __device__ __forceinline__ void pipelined_routes2(int RT, int rt_full, Score&& s
 // resident X and Y fragments take 128 of each wave's 256 registers).
 constexpr int dec_waves(int) { return 8; }
 
+static int decode_pair_elems(int C, int D, int Mp) {  // a stage buffer of the four-wave form
+  const int qz = (D == 16 ? 2 : 1) * (Mp * D + (int)z_frag_elems_per_head(Mp, D));
+  return std::max(qz, (C / 16) * kFrag);
+}
+
 int decode_stage_elems(int C, int D, int Mp) {
   const int hpg = D == 16 ? 2 : 1, gb = D == 64 ? 2 : 1;
   const int head_stage = gb * (C / 16) * kFrag + hpg * (Mp * D + (int)z_frag_elems_per_head(Mp, D));
@@ -936,37 +941,57 @@ bool decode_fused_fits(int C, int D, int Mp, int elem_bytes) {
   return decode_kind_fits(decode_kind(C, D, Mp, elem_bytes), C, D, Mp, elem_bytes);
 }
 
-// Issue the global -> LDS copy of decode stage s into buffer s & 1: for
-// s < HG [key weight slice][q fragments of the group's heads][z fragments of
-// them]; for s = HG + cb the W_O fragments of output block cb.
-template <typename T, int D, int KSC>
+// LDS: with eight waves two buffers, stage s in buffer s & 1: for s < HG
+// [key weight slice][q fragments of the group's heads][z fragments of them],
+// for s = HG + cb the W_O fragments of output block cb.  With four, one key
+// weight slice ahead of the two buffers.
+template <typename T, int D, int KSC, int NW>
+__device__ __forceinline__ void decode_weight_issue(const DecFusedParams& p, char* dst, int s) {
+  constexpr int GB = (D == 64) ? 2 : 1, WELEMS = GB * KSC * kFrag;
+  copy_to_lds((const T*)p.wkf + (int64_t)s * WELEMS, dst, WELEMS * (int)sizeof(T) / 16, 64 * NW);
+}
+
+template <typename T, int D, int KSC, int NW>
 __device__ __forceinline__ void decode_stage_issue(const DecFusedParams& p, char* smem, int SE, int b, int s) {
   constexpr int HPG = (D == 16) ? 2 : 1, GB = (D == 64) ? 2 : 1;
   constexpr int C = KSC * 16, HG = C / 32 / GB, WELEMS = GB * KSC * kFrag;
-  constexpr int NT = 64 * dec_waves(C), per16 = 16 / (int)sizeof(T);
-  char* dst = smem + (size_t)(s & 1) * SE * sizeof(T);
+  constexpr int NT = 64 * NW, per16 = 16 / (int)sizeof(T);
+  char* dst = smem + ((size_t)(s & 1) * SE + (NW == 4 ? WELEMS : 0)) * sizeof(T);
   if (s >= HG) {
     copy_to_lds((const T*)p.wof + (int64_t)(s - HG) * KSC * kFrag, dst, KSC * kFrag / per16, NT);
     return;
   }
+  if constexpr (NW == 8) {
+    decode_weight_issue<T, D, KSC, NW>(p, dst, s);
+    dst += WELEMS * sizeof(T);
+  }
   const int64_t h0 = (int64_t)b * p.H + (int64_t)s * HPG;
   const int nq = HPG * p.Mp * D;
   const int64_t nz = (int64_t)HPG * z_frag_elems_per_head(p.Mp, D);
-  copy_to_lds((const T*)p.wkf + (int64_t)s * WELEMS, dst, WELEMS / per16, NT);
-  copy_to_lds((const T*)p.q_op + h0 * p.Mp * D, dst + (size_t)WELEMS * sizeof(T), nq / per16, NT);
-  copy_to_lds((const T*)p.z_op + h0 * z_frag_elems_per_head(p.Mp, D), dst + (size_t)(WELEMS + nq) * sizeof(T),
-              (int)(nz / per16), NT);
+  copy_to_lds((const T*)p.q_op + h0 * p.Mp * D, dst, nq / per16, NT);
+  copy_to_lds((const T*)p.z_op + h0 * z_frag_elems_per_head(p.Mp, D), dst + (size_t)nq * sizeof(T), (int)(nz / per16),
+              NT);
 }
 
-template <typename T, int D, int KSC>
-__global__ __launch_bounds__(64 * dec_waves(16 * KSC)) void k_decode_fused(DecFusedParams p) {
+// NW waves of 32 tokens.  The route tiles bound it (exponentials and packs; a
+// wave holds X and Y, 128 registers at C = 256, so a SIMD has two).  With four
+// waves two workgroups share a CU: their barriers and their projection and
+// merge phases fall apart, and the last round of a launch ends half as late.
+// That takes half of the LDS, so the four-wave form holds one key weight slice
+// (refilled after a barrier behind the projection) and doubles q and z only.
+// C = 256, D = 32, eight / four waves: M = 256, 2 x 50,000 tokens 102.7 / 97.3
+// us, 2 x 65,536 108.7 / 100.8, 2 x 150,000 264 / 242; M = 128, 65,536 tokens
+// 43.5 / 41.6; one round half empty: M = 64, 20,000 tokens 31.9 / 24.0.
+template <typename T, int D, int KSC, int NW>
+__global__ __launch_bounds__(64 * NW, 2) void k_decode_fused(DecFusedParams p) {
   using F = typename Frag<T>::type;
   constexpr int HPG = (D == 16) ? 2 : 1, GB = (D == 64) ? 2 : 1;
   constexpr int KS = D / 16, RB = (D + 31) / 32;
   constexpr bool ONES_ROW = (D == 16);
   constexpr int C = KSC * 16, CB = C / 32, HG = CB / GB, H = C / D;
   constexpr int WELEMS = GB * KSC * kFrag;  // key weight slice of one head group
-  constexpr int NW = dec_waves(C), TOK = 32 * NW;
+  constexpr int TOK = 32 * NW;
+  constexpr int WOFF = NW == 4 ? WELEMS : 0;  // the key weight slice ahead of the buffers
   extern __shared__ __attribute__((aligned(16))) char smem[];
   T* bufs = reinterpret_cast<T*>(smem);
   const int SE = p.stage_elems;
@@ -981,12 +1006,13 @@ __global__ __launch_bounds__(64 * dec_waves(16 * KSC)) void k_decode_fused(DecFu
   constexpr int ZC = D < 32 ? D : 32;  // value rows per z fragment
   // constant value-operand rows for D = 16 (after the two stage buffers):
   // 8 ones (row 16, the denominators), then 8 zeros (rows 17 .. 31)
-  const int zconst_off = 2 * SE * (int)sizeof(T);
+  const int zconst_off = (WOFF + 2 * SE) * (int)sizeof(T);
   if (ONES_ROW && threadIdx.x < 2)
     store_frag<T>(reinterpret_cast<T*>(smem + zconst_off) + 8 * threadIdx.x,
                   threadIdx.x == 0 ? fill_frag<T>(1.f) : zero_frag<T>());
 
-  decode_stage_issue<T, D, KSC>(p, smem, SE, b, 0);
+  if constexpr (NW == 4) decode_weight_issue<T, D, KSC, NW>(p, smem, 0);
+  decode_stage_issue<T, D, KSC, NW>(p, smem, SE, b, 0);
   F xf[KSC];
 #pragma unroll
   for (int ks = 0; ks < KSC; ++ks)
@@ -1014,10 +1040,22 @@ __global__ __launch_bounds__(64 * dec_waves(16 * KSC)) void k_decode_fused(DecFu
   }
 
   F yf[KSC];  // decoded tokens, merge B operands (16 channels per k step)
+  // log2 of the softmax normaliser over the routes, for the backward: a
+  // group's is stored behind the barrier that ends it, so that the wait of
+  // the next one covers the store
+  float lse[HPG];
+  auto store_lse = [&](int hg) __attribute__((always_inline)) {
+    if (p.lse2 && xok && g == 0)
+#pragma unroll
+      for (int hh = 0; hh < HPG; ++hh) p.lse2[((int64_t)b * H + hg * HPG + hh) * p.N + xrow] = lse[hh];
+  };
 #pragma unroll
   for (int hg = 0; hg < HG; ++hg) {
-    decode_stage_issue<T, D, KSC>(p, smem, SE, b, hg + 1);
-    const T* sb = bufs + (hg & 1) * SE;
+    if (hg > 0) store_lse(hg - 1);
+    decode_stage_issue<T, D, KSC, NW>(p, smem, SE, b, hg + 1);
+    // the key weight slice, then q and z (sq)
+    const T* sb = NW == 4 ? bufs : bufs + (hg & 1) * SE;
+    const T* sq = NW == 4 ? bufs + WELEMS + (hg & 1) * SE : sb + WELEMS;
     f32x16 ka[GB];
 #pragma unroll
     for (int cb = 0; cb < GB; ++cb) {
@@ -1025,6 +1063,12 @@ __global__ __launch_bounds__(64 * dec_waves(16 * KSC)) void k_decode_fused(DecFu
       for (int e = 0; e < 16; ++e) ka[cb][e] = 0.f;
 #pragma unroll
       for (int ks = 0; ks < KSC; ++ks) mma(ka[cb], load_frag(sb + ((cb * KSC + ks) * 64 + lane) * 8), xf[ks]);
+    }
+    if constexpr (NW == 4) {
+      if (hg + 1 < HG) {  // every wave has read the slice: the next group's
+        lds_barrier();
+        decode_weight_issue<T, D, KSC, NW>(p, smem, hg + 1);
+      }
     }
     // token keys of the group's heads, and the |score| bound (token-key
     // norms x the route-query norm bound); the heads of a group go through
@@ -1045,7 +1089,7 @@ __global__ __launch_bounds__(64 * dec_waves(16 * KSC)) void k_decode_fused(DecFu
     // z operand addresses (bytes into LDS): lanes of value rows walk the
     // head's z fragments; on D = 16 the lanes of rows 16 .. 31 read the
     // constant ones / zeros block instead
-    const char* sbc = reinterpret_cast<const char*>(sb);
+    const char* sqc = reinterpret_cast<const char*>(sq);
     uint32_t zbase[HPG], zstep;
     {
       const bool konst = ONES_ROW && c >= 16;
@@ -1053,7 +1097,7 @@ __global__ __launch_bounds__(64 * dec_waves(16 * KSC)) void k_decode_fused(DecFu
 #pragma unroll
       for (int hh = 0; hh < HPG; ++hh)
         zbase[hh] = konst ? (uint32_t)(zconst_off + (c == 16 ? 0 : 8 * (int)sizeof(T)))
-                          : (uint32_t)((sbc - smem) + (WELEMS + HPG * Mp * D + hh * ZH + (g * ZC + c) * 8) * sizeof(T));
+                          : (uint32_t)((sqc - smem) + (HPG * Mp * D + hh * ZH + (g * ZC + c) * 8) * sizeof(T));
     }
     f32x16 acc[HPG][RB];
     float m[HPG], ls[HPG];
@@ -1075,7 +1119,7 @@ __global__ __launch_bounds__(64 * dec_waves(16 * KSC)) void k_decode_fused(DecFu
       for (int e = 0; e < 16; ++e) sc[e] = 0.f;
 #pragma unroll
       for (int js = 0; js < KS; ++js)
-        mma(sc, load_frag(sb + WELEMS + hh * Mp * D + ((rt * KS + js) * 64 + lane) * 8), kf[hh][js]);
+        mma(sc, load_frag(sq + hh * Mp * D + ((rt * KS + js) * 64 + lane) * 8), kf[hh][js]);
       return sc;
     };
     auto routes = [&](auto sf) __attribute__((always_inline)) {
@@ -1115,7 +1159,6 @@ __global__ __launch_bounds__(64 * dec_waves(16 * KSC)) void k_decode_fused(DecFu
     for (int u = 0; u + GKS < KSC; ++u) yf[u] = yf[u + GKS];
 #pragma unroll
     for (int hh = 0; hh < HPG; ++hh) {
-      const int h = hg * HPG + hh;
       const float den = softmax_denominator<RB, ONES_ROW>(acc[hh], ls[hh], lane);
       const float inv = __builtin_amdgcn_rcpf(den);
 #pragma unroll
@@ -1123,12 +1166,11 @@ __global__ __launch_bounds__(64 * dec_waves(16 * KSC)) void k_decode_fused(DecFu
 #pragma unroll
         for (int hf = 0; hf < 2; ++hf)
           if (rb * 32 + 16 * hf < D) yf[KSC - GKS + hh * KS + 2 * rb + hf] = cvt8<T>(acc[hh][rb], 8 * hf, inv);
-      // log2 of the softmax normaliser over the routes (0 is the shift of the
-      // shift-free tiles), for the backward
-      if (p.lse2 && xok && g == 0) p.lse2[((int64_t)b * H + (h)) * p.N + xrow] = (fast ? 0.f : m[hh]) + __log2f(den);
+      lse[hh] = (fast ? 0.f : m[hh]) + __log2f(den);  // 0 is the shift of the shift-free tiles
     }
     lds_wait_barrier();
   }
+  store_lse(HG - 1);
   if (p.y && xok) store_decoded<T, KSC>((T*)p.y + ((int64_t)b * p.N + xrow) * C, yf, g);
   if (!p.o) return;  // the backward's forward needs Y alone (uniform; every copy has landed)
   // ---- merge: O^T = W_O^T Y^T, one 32-channel output block per stage ----
@@ -1164,8 +1206,8 @@ __global__ __launch_bounds__(64 * dec_waves(16 * KSC)) void k_decode_fused(DecFu
     const int s = HG + cbo;
     if (cbo > 0) store_o(cbo - 1, o_prev, r_prev);
     load_res(cbo, r_cur);
-    if (cbo + 1 < CB) decode_stage_issue<T, D, KSC>(p, smem, SE, b, s + 1);
-    const T* sb = bufs + (s & 1) * SE;
+    if (cbo + 1 < CB) decode_stage_issue<T, D, KSC, NW>(p, smem, SE, b, s + 1);
+    const T* sb = bufs + WOFF + (s & 1) * SE;
     f32x16 o;
 #pragma unroll
     for (int e = 0; e < 16; ++e) o[e] = 0.f;
@@ -2150,14 +2192,24 @@ static hipError_t dec_launch(const DecFusedParams& pp, hipStream_t s) {
       }
     }
     if (p.kind != kDecodeStaged) return hipErrorInvalidValue;
-    {
-      const size_t lds = (2 * (size_t)p.stage_elems + 16) * sizeof(T);  // + the constant rows
-      hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_decode_fused<T, D, KSC>),
+    auto staged = [&](auto waves, size_t lds) {
+      constexpr int W = decltype(waves)::value;
+      const unsigned wgrid = (unsigned)((int64_t)p.B * ((p.N + 32 * W - 1) / (32 * W)));
+      hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_decode_fused<T, D, KSC, W>),
                                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
       if (e != hipSuccess) return e;
-      k_decode_fused<T, D, KSC><<<grid, 64 * NW, lds, s>>>(p);
+      k_decode_fused<T, D, KSC, W><<<wgrid, 64 * W, lds, s>>>(p);
       return hipGetLastError();
+    };
+    // four waves wherever two such workgroups fit a CU's LDS (they were the
+    // faster form at every size measured, above)
+    const int pair = decode_pair_elems(16 * KSC, D, p.Mp);
+    const size_t lds4 = ((D == 64 ? 2 : 1) * KSC * kFrag + 2 * (size_t)pair + (D == 16 ? 16 : 0)) * sizeof(T);
+    if (lds4 <= 80 * 1024) {
+      p.stage_elems = pair;
+      return staged(std::integral_constant<int, 4>{}, lds4);
     }
+    return staged(std::integral_constant<int, 8>{}, (2 * (size_t)p.stage_elems + 16) * sizeof(T));
   }
 }
 
