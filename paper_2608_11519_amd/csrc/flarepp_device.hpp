@@ -22,6 +22,7 @@ typedef __attribute__((ext_vector_type(4))) short s16x4;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(8))) float f32x8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 typedef __attribute__((ext_vector_type(2))) float f32x2;
 
 template <typename T> struct Frag;
@@ -124,7 +125,7 @@ __device__ __forceinline__ void store4(__bf16* p, float a, float b, float c, flo
 }
 
 // One 32-channel output block of this lane's row in the 32x32 accumulator
-// layout (channels 8 q + 4 g .. + 3 hold o[4 q .. 4 q + 3]).  The residual
+// layout (channels 8 q + 4 g .. + 3 are o[4 q .. 4 q + 3]).  The residual
 // is loaded by load_res16 ahead of use, so that a merge issues all its
 // residual loads before it waits for any, and store16 adds it (when has_res)
 // and stores the block.
@@ -137,16 +138,45 @@ __device__ __forceinline__ void load_res16(Res16<T>& res, const T* rp, int g) {
 #pragma unroll
   for (int q = 0; q < 4; ++q) res.r[q] = load_half(rp + 8 * q + 4 * g);
 }
+// v (two 4-channel runs, channels 8 q + 4 g of a 16-channel block) as the 8
+// channels 8 g .. + 7 of that block: the lane halves exchange runs
+// (v_permlane32_swap; lanes c and c + 32 hold the same row and are active
+// together), so that a row is stored 16 bytes per lane.  A decode ends with
+// its stores, 32 rows apart, so each instruction costs its segments and
+// nothing runs beside them: half the instructions (decode kernels, 8 / 16
+// bytes: 65,536 tokens of 128 channels, M = 128, with Y 24.6 / 22.7 us;
+// 131,072 of 64, M = 64, D = 64 14.2 / 11.9; 262,144 of 128, M = 64, D = 64
+// 71.6 / 65.8; 2^18 of 128, M = 512, with Y 193 / 181).
+__device__ __forceinline__ bf16x8 runs_of_8(const bf16x8& v) {
+  const u32x4 u = __builtin_bit_cast(u32x4, v);
+  const auto a = __builtin_amdgcn_permlane32_swap(u[0], u[2], false, false);
+  const auto b = __builtin_amdgcn_permlane32_swap(u[1], u[3], false, false);
+  const u32x4 r = {a[0], b[0], a[1], b[1]};
+  return __builtin_bit_cast(bf16x8, r);
+}
+// 8 values of a row in that order: channels 8 q + 4 g .. + 3 in v[4 q ..]
+__device__ __forceinline__ void store_runs(__bf16* p, const float (&v)[8], int g) {
+  bf16x8 w;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) w[e] = (__bf16)v[e];
+  *reinterpret_cast<bf16x8*>(p + 8 * g) = runs_of_8(w);
+}
+__device__ __forceinline__ void store_runs(float* p, const float (&v)[8], int g) {
+  store4(p + 4 * g, v[0], v[1], v[2], v[3]);
+  store4(p + 8 + 4 * g, v[4], v[5], v[6], v[7]);
+}
 template <typename T>
 __device__ __forceinline__ void store16(T* op, const f32x16& o, const Res16<T>& res, bool has_res, int g) {
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    float v[4] = {o[4 * q], o[4 * q + 1], o[4 * q + 2], o[4 * q + 3]};
+  for (int q = 0; q < 2; ++q) {
+    float v[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = o[8 * q + e];
     if (has_res) {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) v[e] += to_f32(res.r[q][e]);
+      for (int e = 0; e < 8; ++e) v[e] += to_f32(res.r[2 * q + e / 4][e % 4]);
     }
-    store4(op + 8 * q + 4 * g, v[0], v[1], v[2], v[3]);
+    store_runs(op + 16 * q, v, g);
   }
 }
 

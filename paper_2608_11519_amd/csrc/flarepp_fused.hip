@@ -865,16 +865,13 @@ __global__ __launch_bounds__(256) void k_combine_par(CombineParams p) {
 // stored per head, the next stage's barrier would wait for them right away.
 template <typename T, int KSC>
 __device__ __forceinline__ void store_decoded(T* yp, const typename Frag<T>::type (&yf)[KSC], int g) {
-  using Half = typename Frag<T>::half;
 #pragma unroll
-  for (int i = 0; i < KSC; ++i)
+  for (int i = 0; i < KSC; ++i) {
+    float v[8];
 #pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      Half v;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) v[e] = yf[i][4 * q + e];
-      *reinterpret_cast<Half*>(yp + 16 * i + 8 * q + 4 * g) = v;
-    }
+    for (int e = 0; e < 8; ++e) v[e] = to_f32(yf[i][e]);
+    store_runs(yp + 16 * i, v, g);
+  }
 }
 
 // Route tiles of the HPG heads of a group, software pipelined over the
@@ -1189,13 +1186,15 @@ __global__ __launch_bounds__(64 * NW, 2) void k_decode_fused(DecFusedParams p) {
     if (xok) {
       T* op = (T*)p.o + ((int64_t)b * p.N + xrow) * C + 32 * cbo;
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        float v[4] = {o[4 * q], o[4 * q + 1], o[4 * q + 2], o[4 * q + 3]};
+      for (int q = 0; q < 2; ++q) {
+        float v[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = o[8 * q + e];
         if (p.res) {
 #pragma unroll
-          for (int e = 0; e < 4; ++e) v[e] += to_f32(r[q][e]);
+          for (int e = 0; e < 8; ++e) v[e] += to_f32(r[2 * q + e / 4][e % 4]);
         }
-        store4(op + 8 * q + 4 * g, v[0], v[1], v[2], v[3]);
+        store_runs(op + 16 * q, v, g);
       }
     }
   };
@@ -1475,13 +1474,16 @@ __global__ __launch_bounds__(64 * dec_waves(16 * KSC)) void k_decode2(DecFusedPa
       if (p.lse2 && xok && g == 0) p.lse2[((int64_t)b * p.H + (hg * HPG + hh)) * p.N + xrow] = (fast ? 0.f : m[hh]) + __log2f(den);
       if (p.y && xok) {
         T* yp = (T*)p.y + ((int64_t)b * p.N + xrow) * C + (hg * HPG + hh) * D;
-        constexpr int NQ4 = ONES_ROW ? 2 : 4;
+        constexpr int NQ8 = ONES_ROW ? 1 : 2;
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
-          for (int q = 0; q < NQ4; ++q)
-            store4(yp + rb * 32 + 8 * q + 4 * g, acc[hh][rb][4 * q] * inv, acc[hh][rb][4 * q + 1] * inv,
-                   acc[hh][rb][4 * q + 2] * inv, acc[hh][rb][4 * q + 3] * inv);
+          for (int q = 0; q < NQ8; ++q) {
+            float v[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] = acc[hh][rb][8 * q + e] * inv;
+            store_runs(yp + rb * 32 + 16 * q, v, g);
+          }
       }
     }
 #pragma unroll
@@ -1797,13 +1799,16 @@ __global__ __launch_bounds__(64 * dec_waves(16 * KSC)) void k_decode3(DecFusedPa
       if (p.lse2 && xok && g == 0) p.lse2[((int64_t)b * p.H + (hg * HPG + hh)) * p.N + xrow] = (fast ? 0.f : m[hh]) + __log2f(den);
       if (p.y && xok) {
         T* yp = (T*)p.y + ((int64_t)b * p.N + xrow) * C + (hg * HPG + hh) * D;
-        constexpr int NQ4 = ONES_ROW ? 2 : 4;
+        constexpr int NQ8 = ONES_ROW ? 1 : 2;
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
-          for (int q = 0; q < NQ4; ++q)
-            store4(yp + rb * 32 + 8 * q + 4 * g, acc[hh][rb][4 * q] * inv, acc[hh][rb][4 * q + 1] * inv,
-                   acc[hh][rb][4 * q + 2] * inv, acc[hh][rb][4 * q + 3] * inv);
+          for (int q = 0; q < NQ8; ++q) {
+            float v[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] = acc[hh][rb][8 * q + e] * inv;
+            store_runs(yp + rb * 32 + 16 * q, v, g);
+          }
       }
     }
   }

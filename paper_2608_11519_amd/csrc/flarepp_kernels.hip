@@ -605,9 +605,12 @@ __global__ __launch_bounds__(256) void k_route(RouteParams p) {
 #pragma unroll
       for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
-        for (int q = 0; q < NQ4; ++q)
-          store4(yp + rb * 32 + 8 * q + 4 * g, acc[i][rb][4 * q] * inv, acc[i][rb][4 * q + 1] * inv,
-                 acc[i][rb][4 * q + 2] * inv, acc[i][rb][4 * q + 3] * inv);
+        for (int q = 0; q < NQ4 / 2; ++q) {
+          float v[8];
+#pragma unroll
+          for (int e = 0; e < 8; ++e) v[e] = acc[i][rb][8 * q + e] * inv;
+          store_runs(yp + rb * 32 + 16 * q, v, g);
+        }
     }
   }
 }
