@@ -791,8 +791,10 @@ __global__ __launch_bounds__(256) void k_combine_par(CombineParams p) {
     a *= w0;
 #pragma unroll
     for (int u = 0; u < kCombineBatch; ++u) {
-      const float w = weight(ml[u][0], mn);
-      if (w != 0.f) {  // (an unread or empty partial may hold anything)
+      // an unread or empty partial may hold anything; any other one counts
+      // also where its weight is zero (zero times an infinity is a NaN)
+      if (ml[u][0] != -INFINITY) {
+        const float w = __builtin_amdgcn_exp2f(ml[u][0] - mn);
         l += ml[u][1] * w;
         a += ar[u] * w;
       }
