@@ -743,116 +743,155 @@ __global__ __launch_bounds__(64 * W) void k_encode_fused(EncFusedParams p) {
 }
 
 // ---------------------------------------------------------------------------
-// Exact merge of split-key partials, parallel over chunk slices.  A block of
-// 256 threads owns 16 rows; 16 lanes share a row, as D / 4 runs of 4 channels
-// times 64 / D chunk slices (slice rg folds chunks rg, rg + 64 / D, ... in
-// order, kCombineBatch of them at a time: one memory round trip, one rescale
-// by the batch's maximum), then a row's slices are folded pairwise.  A slice
-// reads whole rows of neighbouring lanes, and only 4 channels per lane are
-// exchanged (a thread that held all D of a row spent 4 folds of D + 2 lane
-// exchanges; 16 chunks: 6.3 and 5.2 us at 4 x 16,384 x 128, now 5.8 and 4.7; D = 32 at
-// 2 x 50,000 x 256: 9.1 and 7.4, now 6.8 and 5.1).
+// Exact merge of split-key partials, parallel over chunk slices.  LPR lanes
+// share a row, as D / 4 runs of 4 channels times RG chunk slices (slice rg
+// folds chunks rg, rg + RG, ... in order, up to NB of them at a time: one memory
+// round trip, one rescale by the batch's maximum), then a row's slices are
+// folded pairwise.  A slice reads whole rows of neighbouring lanes, and only 4
+// channels per lane are exchanged.  What bounds it is the chain of round
+// trips, in two forms:
+//  * few chunks (one batch of 8 per slice, 16 lanes per row): many rows, so
+//    the registers of small batches keep more waves in flight;
+//  * many chunks come with few rows (the encode's plan fills the CUs with
+//    one or the other): 64 partials of a row in flight at every D, by batches of
+//    16 and D lanes per row.
+// us, few / many form, by rocprof: 4 chunks of 16,384 rows 4.0 / 5.7 (D = 16),
+// 4.2 / 8.5 (32), 5.8 / 19.1 (64); 157 chunks of 128 rows 8.8 / 7.6, 14.3 / 7.7,
+// 25.8 / 7.6; 512 chunks 22 / 16, 39 / 17, 76 / 16.  With the loads behind the
+// tests of the maxima, where the compiler puts them, a batch takes two round
+// trips: 64 chunks of 128 rows 5.0 us (D = 16), now 4.6.
 // ---------------------------------------------------------------------------
-constexpr int kCombineBatch = 8;
+constexpr bool combine_many(int R, int D) { return R > 8 * (64 / D); }
 
-template <typename T, int D>
+template <typename T, int D, bool MANY>
 __global__ __launch_bounds__(256) void k_combine_par(CombineParams p) {
-  constexpr int KS = D / 16, DQ = D / 4, RG = 16 / DQ;
+  constexpr int LPR = MANY ? D : 16;
+  constexpr int KS = D / 16, DQ = D / 4, RG = LPR / DQ, ROWS = 256 / LPR;
   const int t = threadIdx.x, d = 4 * (t % DQ), rg = t / DQ % RG;
   // this thread's first preparation item: loads now, store at the end
   const int64_t pi0 = (int64_t)threadIdx.x * gridDim.x + blockIdx.x;
   typename Frag<T>::type pv;
   if (pi0 < p.prep_n) pv = prep_load<T>(p.prep, pi0);
-  const int rows_per_bh = p.Mp / 16;
-  const int64_t bh = blockIdx.x / rows_per_bh;
-  const int qrow = (blockIdx.x % rows_per_bh) * 16 + (t >> 4);
-  float m = -INFINITY, l = 0.f;
-  f32x4 a = {0.f, 0.f, 0.f, 0.f};
-  // an empty chunk is (-inf, 0, 0): weight 0, whatever the maximum
-  auto weight = [](float mr, float mn) __attribute__((always_inline)) {
-    return mr == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mr - mn);
-  };
-  for (int r0 = rg; r0 < p.R; r0 += RG * kCombineBatch) {
-    f32x2 ml[kCombineBatch];
-    f32x4 ar[kCombineBatch];
+  const int groups = p.Mp / ROWS;  // of rows, per (b, h)
+  for (int64_t blk = blockIdx.x; blk < p.BH * groups; blk += gridDim.x) {
+    const int64_t bh = blk / groups;
+    const int qrow = (int)(blk % groups) * ROWS + t / LPR;
+    float m = -INFINITY, l = 0.f;
+    f32x4 a = {0.f, 0.f, 0.f, 0.f};
+    // an empty chunk is (-inf, 0, 0): weight 0, whatever the maximum
+    auto weight = [](float mr, float mn) __attribute__((always_inline)) {
+      return mr == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mr - mn);
+    };
+    auto fold = [&](auto batch, int r0) __attribute__((always_inline)) {
+      constexpr int NB = decltype(batch)::value;
+      f32x2 ml[NB];
+      f32x4 ar[NB];
 #pragma unroll
-    for (int u = 0; u < kCombineBatch; ++u) {
-      const int r = r0 + RG * u;
-      const int64_t pidx = (bh * p.R + min(r, p.R - 1)) * p.Mp + qrow;
-      ml[u] = *reinterpret_cast<const f32x2*>(p.part_ml + pidx * 2);
-      ar[u] = *reinterpret_cast<const f32x4*>(p.part_acc + pidx * D + d);
-      if (r >= p.R) ml[u][0] = -INFINITY;
-    }
-    float mn = m;
+      for (int u = 0; u < NB; ++u) {
+        const int64_t pidx = (bh * p.R + min(r0 + RG * u, p.R - 1)) * p.Mp + qrow;
+        ml[u] = *reinterpret_cast<const f32x2*>(p.part_ml + pidx * 2);
+        ar[u] = *reinterpret_cast<const f32x4*>(p.part_acc + pidx * D + d);
+      }
+      // every load of the batch is issued before the first value is used (the
+      // compiler moved loads behind the tests of the maxima)
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int u = 0; u < kCombineBatch; ++u) mn = fmaxf(mn, ml[u][0]);
-    const float w0 = weight(m, mn);
-    l *= w0;
-    a *= w0;
+      for (int u = 0; u < NB; ++u) asm volatile("; partial %0 %1" : "+v"(ml[u]), "+v"(ar[u]));
+      float mn = m;
 #pragma unroll
-    for (int u = 0; u < kCombineBatch; ++u) {
-      // an unread or empty partial may hold anything; any other one counts
-      // also where its weight is zero (zero times an infinity is a NaN)
-      if (ml[u][0] != -INFINITY) {
+      for (int u = 0; u < NB; ++u) {
+        if (r0 + RG * u >= p.R) ml[u][0] = -INFINITY;
+        mn = fmaxf(mn, ml[u][0]);
+      }
+      const float w0 = weight(m, mn);
+      l *= w0;
+      a *= w0;
+#pragma unroll
+      for (int u = 0; u < NB; ++u) {
+        // an unread or empty partial may hold anything; any other one counts
+        // also where its weight is zero (zero times an infinity is a NaN)
+        const bool on = ml[u][0] != -INFINITY;
         const float w = __builtin_amdgcn_exp2f(ml[u][0] - mn);
-        l += ml[u][1] * w;
-        a += ar[u] * w;
+        l += on ? ml[u][1] * w : 0.f;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) a[j] += on ? ar[u][j] * w : 0.f;
       }
+      m = mn;
+    };
+    // (uniform branches; a batch reads no more than half in vain)
+    if constexpr (MANY) {
+      int r0 = 0;
+      for (; r0 + 8 * RG < p.R; r0 += 16 * RG) fold(std::integral_constant<int, 16>{}, r0 + rg);
+      if (r0 < p.R) fold(std::integral_constant<int, 8>{}, r0 + rg);
+    } else if (p.R <= RG) {
+      fold(std::integral_constant<int, 1>{}, rg);
+    } else if (p.R <= 2 * RG) {
+      fold(std::integral_constant<int, 2>{}, rg);
+    } else if (p.R <= 4 * RG) {
+      fold(std::integral_constant<int, 4>{}, rg);
+    } else {
+      fold(std::integral_constant<int, 8>{}, rg);
     }
-    m = mn;
-  }
 #pragma unroll
-  for (int k = DQ; k < 16; k <<= 1) {
-    f32x4 ao;
+    for (int k = DQ; k < LPR; k <<= 1) {
+      f32x4 ao;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) ao[j] = __shfl_xor(a[j], k, 64);
-    const float mo = __shfl_xor(m, k, 64), lo = __shfl_xor(l, k, 64);
-    const float mn = fmaxf(m, mo), wa = weight(m, mn), wb = weight(mo, mn);
-    l = l * wa + lo * wb;
-    a = a * wa + ao * wb;
-    m = mn;
-  }
-  const bool valid = qrow < p.M;
-  const float inv = (valid && l > 0.f) ? 1.f / l : 0.f;
-  const int qb = qrow >> 5, qc = qrow & 31;
-  const f32x4 out = a * inv;
-  if (p.frag && p.q_op && p.qnorm2) {
-    // max over the wave's 4 rows of |scaled q|^2 (of the rounded operand),
-    // one entry per wave
-    float n2 = 0.f;
-    if (valid) {
+      for (int j = 0; j < 4; ++j) ao[j] = __shfl_xor(a[j], k, 64);
+      const float mo = __shfl_xor(m, k, 64), lo = __shfl_xor(l, k, 64);
+      const float mn = fmaxf(m, mo), wa = weight(m, mn), wb = weight(mo, mn);
+      l = l * wa + lo * wb;
+      a = a * wa + ao * wb;
+      m = mn;
+    }
+    const bool valid = qrow < p.M;
+    const float inv = (valid && l > 0.f) ? 1.f / l : 0.f;
+    const int qb = qrow >> 5, qc = qrow & 31;
+    const f32x4 out = a * inv;
+    if (p.frag && p.q_op && p.qnorm2) {  // uniform
+      // max over 4 rows (1, 2 or 4 waves) of |scaled q|^2 (of the rounded operand)
+      __shared__ float wave_n2[4];
+      float n2 = 0.f;
+      if (valid) {
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const float q = to_f32(from_f32<T>(out[j] * p.qscale));
-        n2 = __builtin_fmaf(q, q, n2);
+        for (int j = 0; j < 4; ++j) {
+          const float q = to_f32(from_f32<T>(out[j] * p.qscale));
+          n2 = __builtin_fmaf(q, q, n2);
+        }
       }
-    }
 #pragma unroll
-    for (int k = 1; k < DQ; k <<= 1) n2 += __shfl_xor(n2, k, 64);
-    n2 = fmaxf(n2, __shfl_xor(n2, 16, 64));
-    n2 = fmaxf(n2, __shfl_xor(n2, 32, 64));
-    if ((t & 63) == 0) p.qnorm2[bh * (p.Mp / 4) + (blockIdx.x % rows_per_bh) * 4 + (t >> 6)] = n2;
-  }
-  if (rg == 0) {
-    const float q = p.qscale;
-    if (valid && p.out32) store4(p.out32 + (bh * p.M + qrow) * D + d, out[0], out[1], out[2], out[3]);
-    if (p.q_op) {  // rows, or q fragment order
-      const int64_t off = p.frag ? (int64_t)bh * p.Mp * D + ((int64_t)(qb * KS + (d >> 4)) * 64 + ((d >> 3) & 1) * 32 + qc) * 8 + (d & 7)
-                                 : (bh * p.Mp + qrow) * D + d;
-      store4((T*)p.q_op + off, out[0] * q, out[1] * q, out[2] * q, out[3] * q);
-    }
-    if (p.z_op) {
-      if (!p.frag) {
+      for (int k = 1; k < DQ; k <<= 1) n2 += __shfl_xor(n2, k, 64);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) ((T*)p.z_op)[(bh * D + d + j) * p.Mp + qrow] = from_f32<T>(out[j]);
-      } else {  // z fragment order; row qc of route tile qb
-        const int hf = qc >> 4, rr = qc & 15, gz = (rr >> 2) & 1, jj = 4 * (rr >> 3) + (rr & 3);
-        T* z = (T*)p.z_op + bh * z_frag_elems_per_head(p.Mp, D);
+      for (int k = LPR; k < 64; k <<= 1) n2 = fmaxf(n2, __shfl_xor(n2, k, 64));
+      if (LPR > 16) {
+        __syncthreads();  // the last group's maxima have been read
+        if (lane_id() == 0) wave_n2[wave_id()] = n2;
+        __syncthreads();
 #pragma unroll
-        for (int j = 0; j < 4; ++j) z[z_frag_index(qb, hf, (d + j) >> 5, gz, (d + j) & 31, jj, D)] = from_f32<T>(out[j]);
+        for (int w = 1; w < LPR / 16; ++w) n2 = fmaxf(n2, wave_n2[min(wave_id() + w, 3)]);
       }
+      if (t % (4 * LPR) == 0) p.qnorm2[bh * (p.Mp / 4) + (qrow >> 2)] = n2;
     }
-    if (valid && p.lse && d == 0) p.lse[bh * p.M + qrow] = 0.6931471805599453f * (m + __log2f(l));
+    if (rg == 0) {
+      const float q = p.qscale;
+      if (valid && p.out32) store4(p.out32 + (bh * p.M + qrow) * D + d, out[0], out[1], out[2], out[3]);
+      if (p.q_op) {  // rows, or q fragment order
+        const int64_t off = p.frag ? (int64_t)bh * p.Mp * D + ((int64_t)(qb * KS + (d >> 4)) * 64 + ((d >> 3) & 1) * 32 + qc) * 8 + (d & 7)
+                                   : (bh * p.Mp + qrow) * D + d;
+        store4((T*)p.q_op + off, out[0] * q, out[1] * q, out[2] * q, out[3] * q);
+      }
+      if (p.z_op) {
+        if (!p.frag) {
+#pragma unroll
+          for (int j = 0; j < 4; ++j) ((T*)p.z_op)[(bh * D + d + j) * p.Mp + qrow] = from_f32<T>(out[j]);
+        } else {  // z fragment order; row qc of route tile qb
+          const int hf = qc >> 4, rr = qc & 15, gz = (rr >> 2) & 1, jj = 4 * (rr >> 3) + (rr & 3);
+          T* z = (T*)p.z_op + bh * z_frag_elems_per_head(p.Mp, D);
+#pragma unroll
+          for (int j = 0; j < 4; ++j) z[z_frag_index(qb, hf, (d + j) >> 5, gz, (d + j) & 31, jj, D)] = from_f32<T>(out[j]);
+        }
+      }
+      if (valid && p.lse && d == 0) p.lse[bh * p.M + qrow] = 0.6931471805599453f * (m + __log2f(l));
+    }
   }
   if (pi0 < p.prep_n) prep_store<T>(p.prep, pi0, pv);
   for (int64_t k = 1;; ++k) {  // further items (when there are more than threads)
@@ -2116,13 +2155,21 @@ hipError_t launch_encode_fused(const EncFusedParams& p, int D, int waves, hipStr
   return hipErrorInvalidValue;
 }
 
+template <typename T, int D>
+static void combine_go(const CombineParams& p, hipStream_t s) {
+  const bool many = combine_many(p.R, D);
+  // (a launch holds fewer than 2^32 threads)
+  const unsigned grid = (unsigned)std::min<int64_t>(p.BH * (p.Mp / (many ? 256 / D : 16)), 1 << 23);
+  if (many) k_combine_par<T, D, true><<<grid, 256, 0, s>>>(p);
+  else k_combine_par<T, D, false><<<grid, 256, 0, s>>>(p);
+}
+
 template <typename T>
 hipError_t launch_combine_par(const CombineParams& p, hipStream_t s) {
-  const unsigned grid = (unsigned)(p.BH * (p.Mp / 16));
   switch (p.D) {
-    case 16: k_combine_par<T, 16><<<grid, 256, 0, s>>>(p); break;
-    case 32: k_combine_par<T, 32><<<grid, 256, 0, s>>>(p); break;
-    case 64: k_combine_par<T, 64><<<grid, 256, 0, s>>>(p); break;
+    case 16: combine_go<T, 16>(p, s); break;
+    case 32: combine_go<T, 32>(p, s); break;
+    case 64: combine_go<T, 64>(p, s); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
