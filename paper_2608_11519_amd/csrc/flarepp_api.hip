@@ -14,6 +14,7 @@
 
 #include "../../include/flarepp.h"
 #include "flarepp_internal.hpp"
+#include "flarepp_split.hpp"
 
 namespace {
 
@@ -571,42 +572,16 @@ int route_impl(int kind, int dtype, int64_t B, int64_t H, int64_t N, int64_t M, 
 
 
 // ---- backward (App. A.5) ----------------------------------------------------
-// Work split of the SDPA backward over the long axis (keys of an encode,
-// tokens of the decode): chunks per (b, h) and 32-position tiles per wave;
-// and over the routes: a launch covers nsb route blocks (a window), sized so
-// that four waves' route-gradient slots fit the LDS; the windows run one
-// after another.  (bf16 at D = 16 and 32 takes rs_split instead.)
-struct BwdSplit {
-  int waves, R, tpw, nsb;
-};
-
-BwdSplit bwd_split(int64_t BH, int64_t Nl, int D, int Mp, bool dec, int elem_bytes) {
-  BwdSplit sp{};
-  const int NS = Mp / 32;
-  // LDS budget of a window at 4 waves: the kernel's registers hold one wave
-  // per SIMD, so one workgroup takes the CU's LDS, and a smaller window would
-  // only re-read the long side once more per window.  FLAREPP_BWD_WINDOW_KB
-  // (testing and tuning) overrides it.
-  size_t budget = 160 * 1024;
+// LDS budget of a route window of k_attn_bwd at 4 waves: the kernel's registers
+// hold one wave per SIMD, so one workgroup takes the CU's LDS, and a smaller
+// window would only re-read the long side once more per window.
+// FLAREPP_BWD_WINDOW_KB (testing and tuning) overrides it.
+size_t bwd_window_budget() {
   if (const char* f = std::getenv("FLAREPP_BWD_WINDOW_KB")) {
     const long kb = std::atol(f);
-    if (kb >= 16 && kb <= 160) budget = (size_t)kb * 1024;
+    if (kb >= 16 && kb <= 160) return (size_t)kb * 1024;
   }
-  int nwin = 1;
-  while (nwin < NS && flarepp::attn_bwd_lds_bytes(D, (int)cdiv(NS, nwin), Mp, dec, 4, elem_bytes) > budget)
-    ++nwin;
-  sp.nsb = (int)cdiv(NS, nwin);
-  sp.waves = flarepp::attn_bwd_waves(D, sp.nsb, Mp, dec, elem_bytes);
-  const int64_t tiles = cdiv(Nl, 32);
-  // one round of workgroups: a CU holds one (the registers), so a count a
-  // little over 256 leaves a second round nearly empty (1 x 20,011 tokens,
-  // M = 100, D = 16, fp32: 316 workgroups 64, 59 and 56 us, 212 47, 44 and 42)
-  int64_t R = std::max<int64_t>(1, std::min<int64_t>(256 / BH, cdiv(tiles, sp.waves)));
-  const int64_t tpw = cdiv(tiles, R * sp.waves);
-  R = cdiv(tiles, tpw * sp.waves);
-  sp.R = (int)R;
-  sp.tpw = (int)tpw;
-  return sp;
+  return 160 * 1024;
 }
 
 // Split-K of the five token reductions dW = X^T dG, dW_O = Y^T dO (K = B N
@@ -633,7 +608,7 @@ struct BwdWs {
   void *dVlo, *dVtlo;  // bf16: the value gradients' low parts
   void *Qr, *Qt, *Zr, *dZr, *dZt, *dQr, *dQt, *Sr, *St;
   void* lc;  // register-resident routes: -L and -c of the decode's positions
-  BwdSplit dec, enc;
+  flarepp::BwdSplit dec, enc;
   flarepp::RsSplit rs;
   int splits, kchunk;
   int wg_prob; int64_t wg_chunk;  // k_wgrad's problems and tokens per chunk
@@ -727,8 +702,8 @@ BwdWs bwd_ws(void* base, int dtype, int64_t B, int64_t N, int64_t C, int64_t H, 
     w.dQt = cv.take(bs * BH * Mp * 32 * DB);
     w.Sr = cv.take(bs * H * Mp * D);
     w.St = cv.take(bs * H * Mp * 32 * DB);
-    w.dec = bwd_split(BH, N, (int)D, (int)Mp, true, (int)bs);
-    w.enc = bwd_split(BH, N, (int)D, (int)Mp, false, (int)bs);
+    w.dec = flarepp::bwd_split(BH, N, (int)D, (int)Mp, true, (int)bs, bwd_window_budget());
+    w.enc = flarepp::bwd_split(BH, N, (int)D, (int)Mp, false, (int)bs, bwd_window_budget());
   }
   const int64_t R = std::max<int64_t>(std::max(w.dec.R, w.enc.R), 1);
   w.pa = (float*)cv.take(f4 * BH * R * Mp * D);
@@ -917,7 +892,7 @@ int backward_impl(int dtype, int64_t B, int64_t N, int64_t C, int64_t H, int64_t
 
   // one SDPA backward, launched once per window of route blocks; the later
   // windows add to the long-side gradients of the earlier ones
-  auto attn_windows = [&](const AttnBwdParams& a, const BwdSplit& sp, bool dec) -> int {
+  auto attn_windows = [&](const AttnBwdParams& a, const flarepp::BwdSplit& sp, bool dec) -> int {
     const int NS = (int)(Mp / 32);
     for (int w0 = 0; w0 < NS; w0 += sp.nsb) {
       AttnBwdParams q = a;

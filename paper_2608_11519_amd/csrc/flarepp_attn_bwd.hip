@@ -46,6 +46,7 @@
 
 #include "flarepp_device.hpp"
 #include "flarepp_internal.hpp"
+#include "flarepp_split.hpp"
 
 namespace flarepp {
 namespace {
@@ -106,7 +107,6 @@ __device__ __forceinline__ bf16x8 pack8(const f32x16& a, int o) {
 template <int D> constexpr int rs_pt() { return D == 16 ? 2 : 1; }
 template <int D, bool DEC> constexpr int rs_pieces() { return (DEC ? 1 : 2) * (D == 16 ? 2 : 4); }
 // Bytes: one stage (position rows of a step), one partial buffer.
-constexpr int rs_positions(int D, int rw) { return (8 / rw) * (D == 16 ? 2 : 1) * 32; }
 constexpr int rs_stage_bytes(int D, bool dec, int rw) { return rs_positions(D, rw) * (4 * D + (dec ? 16 : 0)); }
 // (one route group: the waves' 2 KiB scratch, over both buffers)
 constexpr int rs_part_bytes(int D, bool dec, int rw) {
@@ -633,33 +633,6 @@ hipError_t rs_go(const AttnBwdRsParams& p, hipStream_t s) {
 }
 
 }  // namespace
-
-RsSplit rs_split(int64_t B, int64_t H, int64_t N, int D, int Mp) {
-  RsSplit sp{};
-  sp.rb = 1;
-  const int NS = Mp / 32;
-  // route blocks per wave: what the registers hold next to the tile's work
-  const int cap = D == 16 ? 4 : 2;
-  while (sp.rb < cap && sp.rb < NS) sp.rb *= 2;
-  // route groups: the fewest (a power of two) that hold the routes, at most 8
-  while (sp.rw_log2 < 3 && (sp.rb << sp.rw_log2) < NS) ++sp.rw_log2;
-  sp.nbw = sp.rb << sp.rw_log2;
-  const int64_t SP = rs_positions(D, 1 << sp.rw_log2), steps = (N + SP - 1) / SP, BH = B * H;
-  // chunks: one workgroup per CU; with more (b, h) pairs than CUs, the count
-  // whose last round of workgroups is fullest
-  int64_t R = std::max<int64_t>(1, 256 / BH);
-  if (BH > 128) {
-    double best = 1e30;
-    for (int64_t x = 1; x <= 4; ++x) {
-      const double t = (double)((BH * x + 255) / 256) / (double)x * (1.0 + 0.02 * (double)x);
-      if (t < best) { best = t; R = x; }
-    }
-  }
-  R = std::min(R, steps);
-  sp.steps = (int)((steps + R - 1) / R);
-  sp.R = (int)((steps + sp.steps - 1) / sp.steps);
-  return sp;
-}
 
 hipError_t launch_attn_bwd_rs(const AttnBwdRsParams& p, int D, bool dec, int rb, hipStream_t s) {
   if (D == 16) {

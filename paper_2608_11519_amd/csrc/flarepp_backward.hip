@@ -25,6 +25,7 @@
 
 #include "flarepp_device.hpp"
 #include "flarepp_internal.hpp"
+#include "flarepp_split.hpp"
 
 namespace flarepp {
 namespace {
@@ -322,16 +323,8 @@ __global__ __launch_bounds__(256) void k_sum_splits(const float* part, SumOuts o
 // ---------------------------------------------------------------------------
 // SDPA backward over a chunk of the long axis
 // ---------------------------------------------------------------------------
-// LDS per wave: the short-side slot(s) [D][Mp + 4] fp32 (route index fastest,
-// padded so that the lanes' rows fall in different banks) and one transpose
-// tile [32][32 + 16 bytes] of T (dS, then P in the decode); per workgroup
-// (encode) the routes' L and c.
+// Row pitch of a wave's transpose tile.
 template <typename T> constexpr int tb_pitch() { return 32 + 16 / (int)sizeof(T); }
-// Bytes of a wave's transpose tile.
-constexpr size_t attn_bwd_tile_bytes(int elem_bytes) { return (size_t)32 * (32 + 16 / elem_bytes) * elem_bytes; }
-size_t attn_bwd_wave_bytes(int D, int nsb, bool dec, int elem_bytes) {
-  return sizeof(float) * (size_t)(dec ? 2 : 1) * D * (32 * nsb + 4) + attn_bwd_tile_bytes(elem_bytes);
-}
 
 // Fragment of a long-side row: element j = x[n * sn + (d0 + j) * sd] (one
 // 16-byte load when the row is contiguous), zero when !ok.  The caller passes
@@ -906,16 +899,6 @@ hipError_t attn_bwd_go(const AttnBwdParams& p, hipStream_t s) {
 }
 
 }  // namespace
-
-int attn_bwd_waves(int D, int nsb, int Mp, bool dec, int elem_bytes) {
-  for (int w = 4; w >= 1; w /= 2)
-    if (attn_bwd_lds_bytes(D, nsb, Mp, dec, w, elem_bytes) <= 160 * 1024) return w;
-  return 0;
-}
-
-size_t attn_bwd_lds_bytes(int D, int nsb, int Mp, bool dec, int waves, int elem_bytes) {
-  return (size_t)waves * attn_bwd_wave_bytes(D, nsb, dec, elem_bytes) + (dec ? 0 : 2 * sizeof(float) * (size_t)Mp);
-}
 
 int gemm_tile(int n) { return n >= 128 ? 128 : 64; }
 

@@ -373,16 +373,6 @@ hipError_t rows_sum_go(const RowsSumParams& p, hipStream_t s) {
 
 }  // namespace
 
-// Chunks of tokens: one round of workgroups over the 256 CUs, a multiple of 8
-// (one XCD each) where there are that many, at least 128 tokens each.
-int wgrad_chunks(int64_t T, int nprob, int64_t* chunk) {
-  int64_t n = std::max<int64_t>(1, 256 / nprob);
-  if (n >= 8) n = n / 8 * 8;
-  n = std::min(n, (T + 127) / 128);
-  *chunk = ((T + n - 1) / n + 31) / 32 * 32;
-  return (int)((T + *chunk - 1) / *chunk);
-}
-
 hipError_t launch_wgrad(const WgradParams& p, int C, hipStream_t s) {
   return C == 64 ? wgrad_go<64>(p, s) : C == 128 ? wgrad_go<128>(p, s) : wgrad_go<256>(p, s);
 }

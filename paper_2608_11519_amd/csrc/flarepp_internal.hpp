@@ -298,12 +298,7 @@ struct AttnBwdRsParams {
   void* dg; void* dg_lo; int acc_g;
   float* part_a; float* part_g;
 };
-struct RsSplit {
-  int rb, rw_log2, nbw;  // route blocks per wave, log2 route groups, route blocks per launch
-  int R, steps;
-};
 constexpr bool rs_ok(int D, int elem_bytes) { return elem_bytes == 2 && (D == 16 || D == 32); }
-RsSplit rs_split(int64_t B, int64_t H, int64_t N, int D, int Mp);
 hipError_t launch_attn_bwd_rs(const AttnBwdRsParams&, int D, bool dec, int rb, hipStream_t);
 constexpr float kNoMass = -1e30f;  // log2 weight of an excluded route or position (finite: times 0 is 0)
 
@@ -331,14 +326,9 @@ struct RowsSumParams {
   int64_t T;
 };
 constexpr bool grad_gemm_ok(int C, int elem_bytes) { return elem_bytes == 2 && (C == 64 || C == 128 || C == 256); }
-int wgrad_chunks(int64_t T, int nprob, int64_t* chunk);
 hipError_t launch_wgrad(const WgradParams&, int C, hipStream_t);
 hipError_t launch_wgrad_sum(const WgradSumParams&, hipStream_t);
 hipError_t launch_rows_sum(const RowsSumParams&, int C, hipStream_t);
-// LDS of a launch over a window of nsb route blocks (Mp routes in all)
-int attn_bwd_waves(int D, int nsb, int Mp, bool dec, int elem_bytes);
-size_t attn_bwd_lds_bytes(int D, int nsb, int Mp, bool dec, int waves, int elem_bytes);
-
 // Fixed-order sums of backward partials: out[o][m][d] =
 // sum_{p < P} (sum_{r < R0} part0[p][o][r][m][d] + sum_{r < R1} part1[p][o][r][m][d]),
 // partials laid out [P][O][R][Mp][D] fp32 (part1 and R1 zero: none).
