@@ -636,6 +636,26 @@ bool bwd_lo_parts(int dtype) {
 // are still materialised for the reverse pass.
 bool bwd_fused_encodes(int dtype, const MixerPlan& pl) { return pl.fused && dtype == FLAREPP_BF16; }
 
+// Which decode that forward takes for call 3 (given fused encodes).  The fused
+// one projects, decodes and merges; the unfused one reads the K that is
+// materialised anyway, and the merge, for the training forward, is a product.
+// At C = 256 the fused decode walks all head groups in one workgroup, ~26 us
+// however few the tokens, up to about 65,536 (one round of workgroups), where
+// the unfused one takes time by tokens x routes; at C <= 128 the fused one is
+// not the slower for the training forward.  C = 256, us of the training forward
+// and of the whole backward, fused / unfused:
+//   D = 16, M = 32, 1,024 tokens     69.1 /  57.2   153.7 / 134.9
+//   D = 16, M = 256, 32,768 tokens  179.5 / 167.7   455.0 / 438.3  (the line)
+//   D = 16, M = 256, 50,000 tokens  223.2 / 229.0   617.8 / 616.3
+//   D = 32, M = 256, 16,384 tokens  110.4 / 100.8   285.2 / 268.4  (the line)
+//   D = 32, M = 64, 65,536 tokens   187.8 / 189.3   512.8 / 502.5
+//   D = 32, M = 256, 50,000 tokens  184.6 / 192.4   562.2 / 561.8
+//   D = 64, M = 64, 16,384 tokens   105.9 / 105.8   315.5 / 307.5  (the line)
+//   D = 64, M = 64, 65,536 tokens   188.3 / 201.6   742.0 / 746.5
+bool bwd_fused_decode(int64_t T, int64_t C, int64_t D, int64_t Mp) {
+  return C <= 128 || T * std::max<int64_t>(Mp, 64) > int64_t(1) << (D == 16 ? 23 : D == 32 ? 22 : 20);
+}
+
 BwdWs bwd_ws(void* base, int dtype, int64_t B, int64_t N, int64_t C, int64_t H, int64_t M) {
   const int64_t D = C / H, Mp = round_up(M, 32), Np = round_up(N, 32), DB = cdiv(D, 32);
   const size_t bs = dtype_bytes(dtype), f4 = sizeof(float);
@@ -779,17 +799,30 @@ int backward_impl(int dtype, int64_t B, int64_t N, int64_t C, int64_t H, int64_t
   pp.wf[3] = w.wf[3]; pp.out[3] = w.Vtdm; pp.layout[3] = kHeadsDMajor;
   HIPTRY(launch_project<T>(pp, s));
   const MixerPlan pl = mixer_plan(dtype, B, N, C, H, M);
+  // call 3 on the unfused decode (route operands as rows of Q(X) scaled and
+  // Z d-major), which writes Y and the per-token log-normaliser
+  auto unfused_call3 = [&]() -> int {
+    RouteParams r3 = decode_params(B, H, N, M, D);
+    r3.ka = w.q_op; r3.ka_sb = rtBS; r3.ka_sh = rtHS; r3.ka_rows = (int)Mp;
+    r3.va = w.z_op; r3.va_sb = H * D * Mp; r3.va_sh = D * Mp; r3.va_ld = (int)Mp;
+    r3.qs = w.K; r3.qs_sb = tokBS; r3.qs_sh = tokHS; r3.qs_rows = (int)N;
+    r3.y = w.Y; r3.y_sb = N * C; r3.y_row = C; r3.lse2 = w.L3;
+    HIPTRY(launch_route<T>(r3, (int)D, true, s));
+    return FLAREPP_OK;
+  };
   if (bwd_fused_encodes(dtype, pl)) {
-    // the three calls on the fused kernels, as in the forward; the decode
-    // writes Y and the per-token log-normaliser for the reverse pass, and O
-    // for the training forward alone (without it the merge is skipped)
+    // the encodes on the fused kernels, as in the forward.  The decode writes
+    // Y and the per-token log-normaliser for the reverse pass: the fused one
+    // (with O for the training forward; without it the merge is skipped), or
+    // with few tokens the unfused one, whose operands the combines write
+    const bool fdec = bwd_fused_decode(NT, C, D, Mp);
     const int dkind = decode_kind_for((int)C, (int)D, (int)Mp, (int)dtype_bytes(dtype));
     PrepFusedParams fp{};
     fp.C = (int)C;
     fp.w[0] = Wk; fp.wf[0] = w.fwf[0]; fp.mode[0] = kFragKeyPerm;
     fp.w[1] = Wv; fp.wf[1] = w.fwf[1]; fp.mode[1] = kFragPlain;
     fp.w[2] = Wo; fp.wf[2] = w.fwo; fp.mode[2] = dkind == kDecodeStaged ? kFragMerge : kFragMergeHg;
-    fp.nw = 3;
+    fp.nw = fdec ? 3 : 2;
     fp.seeds = seeds; fp.H = (int)H; fp.M = (int)M; fp.Mp = (int)Mp; fp.D = (int)D; fp.qscale = qscale;
     EncFusedParams ep{};
     ep.x = X; ep.wk_raw = Wkt; ep.wv_raw = Wvt; ep.seeds_raw = seeds;
@@ -802,16 +835,19 @@ int backward_impl(int dtype, int64_t B, int64_t N, int64_t C, int64_t H, int64_t
     cp.part_ml = w.part_ml; cp.part_acc = w.part_acc; cp.BH = BH; cp.R = pl.nchunks;
     cp.M = (int)M; cp.Mp = (int)Mp; cp.D = (int)D; cp.qscale = qscale; cp.frag = 1;
     cp.out32 = w.Qf; cp.lse = w.L1; cp.q_op = w.fq_op;
-    cp.qnorm2 = w.fqnorm2;
+    cp.qnorm2 = fdec ? w.fqnorm2 : nullptr; cp.q_rows = fdec ? nullptr : w.q_op;
     cp.prep = fp; cp.prep_n = prep_fused_items(fp);
     HIPTRY(launch_combine_par<T>(cp, s));
     ep.wk_raw = ep.wv_raw = ep.seeds_raw = nullptr;
     ep.wkf = w.fwf[0]; ep.wvf = w.fwf[1]; ep.q_op = w.fq_op; ep.q_sb = H * Mp * D;
     HIPTRY(launch_encode_fused<T>(ep, (int)D, pl.waves, s));
-    cp.out32 = w.Zf; cp.lse = w.L2; cp.q_op = nullptr; cp.qnorm2 = nullptr;
-    cp.z_op = w.fz_op;
+    cp.out32 = w.Zf; cp.lse = w.L2; cp.q_op = nullptr; cp.qnorm2 = nullptr; cp.q_rows = nullptr;
+    cp.frag = fdec ? 1 : 0; cp.z_op = fdec ? w.fz_op : w.z_op;
     cp.prep_n = 0;
     HIPTRY(launch_combine_par<T>(cp, s));
+    if (!fdec) {
+      TRY(unfused_call3());
+    } else {
     DecFusedParams dp{};
     dp.x = X; dp.wkf = w.fwf[0]; dp.wof = w.fwo; dp.q_op = w.fq_op; dp.z_op = w.fz_op; dp.qnorm2 = w.fqnorm2;
     dp.B = (int)B; dp.N = (int)N; dp.C = (int)C; dp.H = (int)H; dp.M = (int)M; dp.Mp = (int)Mp;
@@ -823,6 +859,7 @@ int backward_impl(int dtype, int64_t B, int64_t N, int64_t C, int64_t H, int64_t
     dp.kind = dkind;
     HIPTRY(launch_decode_fused<T>(dp, (int)D, s));
     if (mode == kBwdForward) return ok();
+    }
   } else {
   RoutePrepParams sp{};
   sp.src = seeds; sp.src_bstride = 0; sp.B = 1; sp.H = (int)H; sp.M = (int)M; sp.Mp = (int)Mp;
@@ -846,14 +883,7 @@ int backward_impl(int dtype, int64_t B, int64_t N, int64_t C, int64_t H, int64_t
   CombineParams c2 = c1;
   c2.out32 = w.Zf; c2.lse = w.L2; c2.q_op = nullptr; c2.z_op = w.z_op;
   HIPTRY(launch_combine_par<T>(c2, s));
-  // call 3 (route operands as rows of Q(X) scaled and Z d-major) writes Y and
-  // the per-token log-normaliser
-  RouteParams r3 = decode_params(B, H, N, M, D);
-  r3.ka = w.q_op; r3.ka_sb = rtBS; r3.ka_sh = rtHS; r3.ka_rows = (int)Mp;
-  r3.va = w.z_op; r3.va_sb = H * D * Mp; r3.va_sh = D * Mp; r3.va_ld = (int)Mp;
-  r3.qs = w.K; r3.qs_sb = tokBS; r3.qs_sh = tokHS; r3.qs_rows = (int)N;
-  r3.y = w.Y; r3.y_sb = N * C; r3.y_row = C; r3.lse2 = w.L3;
-  HIPTRY(launch_route<T>(r3, (int)D, true, s));
+  TRY(unfused_call3());
   }
   }
   if (mode == kBwdForward) {  // the training forward's output O = Y W_O (the fused decode returned above)

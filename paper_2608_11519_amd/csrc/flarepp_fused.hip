@@ -879,6 +879,7 @@ __global__ __launch_bounds__(256) void k_combine_par(CombineParams p) {
                                    : (bh * p.Mp + qrow) * D + d;
         store4((T*)p.q_op + off, out[0] * q, out[1] * q, out[2] * q, out[3] * q);
       }
+      if (p.q_rows) store4((T*)p.q_rows + (bh * p.Mp + qrow) * D + d, out[0] * q, out[1] * q, out[2] * q, out[3] * q);
       if (p.z_op) {
         if (!p.frag) {
 #pragma unroll

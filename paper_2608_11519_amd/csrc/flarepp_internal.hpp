@@ -110,6 +110,7 @@ struct CombineParams {
   //  frag == 1: fragment order, see q_frag_index / z_frag_index   (fused)
   int frag;
   void* q_op;
+  void* q_rows;   // the frag == 0 layout of q_op as well, or null
   void* z_op;
   float* qnorm2;  // frag == 1 with q_op: [BH][Mp / 4] max of |scaled q|^2 over
                   // each group of 4 routes (one entry per wave), or null
