@@ -198,13 +198,15 @@ __device__ __forceinline__ void proj_store(const ProjParams& p, int b, int n0, i
                                            const f32x16 (&acc)[NQ], const ProjExtra<T, NQ>* extra = nullptr);
 
 // One unit: tokens [n0, n0 + 32) of batch entry b times column group cg of
-// weight w, whose fragments start at wf (global memory or an LDS copy).
-template <typename T>
+// weight w, whose fragments start at wf (global memory or an LDS copy).  DM:
+// weight w's layout is the d-major one (result rows = tokens); decided outside
+// of the k loop, whose time otherwise hangs on how its branches come to lie
+// (the four projections of 1,024 x 512: 23 or 25 us from build to build, 16 now).
+template <typename T, bool DM>
 __device__ __forceinline__ void proj_unit(const ProjParams& p, int b, int n0, int w, int cg, const T* wf) {
   using F = typename Frag<T>::type;
   const int lane = lane_id(), g = lane >> 5, c = lane & 31;
   const int CB = p.C / 32, KS = p.C / 16;
-  const int layout = p.layout[w];
   const T* X = (const T*)p.x + ((int64_t)b * p.N) * p.C;
   const int xrow = n0 + c;
   const bool xok = xrow < p.N;
@@ -237,8 +239,8 @@ __device__ __forceinline__ void proj_unit(const ProjParams& p, int b, int n0, in
 #pragma unroll
     for (int q = 0; q < kProjBlocks; ++q) {
       if (q >= nq) break;  // wave-uniform
-      if (layout == kHeadsDMajor) mma(acc[q], xf, wv[q]);   // rows = tokens, cols = channels
-      else mma(acc[q], wv[q], xf);                          // rows = channels, cols = tokens
+      if (DM) mma(acc[q], xf, wv[q]);   // rows = tokens, cols = channels
+      else mma(acc[q], wv[q], xf);      // rows = channels, cols = tokens
     }
   }
   proj_store<T>(p, b, n0, w, cg, acc);
@@ -317,7 +319,9 @@ __global__ __launch_bounds__(256) void k_project(ProjParams p) {
   const int cg = (int)(u % CG);
   const int w = (int)((u / CG) % p.nw);
   const int64_t bn = u / ((int64_t)CG * p.nw);
-  proj_unit<T>(p, (int)(bn / NB), (int)(bn % NB) * 32, w, cg, (const T*)p.wf[w]);
+  const int b = (int)(bn / NB), n0 = (int)(bn % NB) * 32;
+  if (p.layout[w] == kHeadsDMajor) proj_unit<T, true>(p, b, n0, w, cg, (const T*)p.wf[w]);  // uniform
+  else proj_unit<T, false>(p, b, n0, w, cg, (const T*)p.wf[w]);
 }
 
 // One unit of the persistent form: the tile's X fragments xf times weight w
