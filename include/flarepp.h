@@ -298,9 +298,11 @@ FLAREPP_API int flarepp_mixer_forward_shared(int dtype, int64_t B, int64_t N, in
  * Sizes as for the mixer; in addition B*N <= 2^30 (FLAREPP_ERR_UNSUPPORTED
  * otherwise).  Workspace:
  * flarepp_mixer_backward_workspace_bytes(...) bytes (0 for an invalid or
- * unsupported shape); it holds the forward's K, V, K~, V~, Y and the token
- * gradients dY, dK, dV, dK~, dV~ (and the low parts of dV, dV~ with bf16),
- * about 10 * bytes(dtype) * B * N * C bytes (12 with bf16).
+ * unsupported shape); it holds the forward's K, V, K~, V~, Y, the token
+ * gradients dY, dK, dV, dK~, dV~ (and the low parts of dV, dV~ with bf16) and
+ * the decode's normalisers: 10 * bytes(dtype) * B * N * C (12 with bf16) +
+ * 4 * B * H * N bytes; beside these, weights, route operands and partial sums,
+ * which do not grow with N beyond one round of workgroups.
  * flarepp_mixer_backward_debug also writes the summed latent gradient dZ and
  * the summed query gradient dQ (fp32 [B][H][M][D] each) when non-null.
  * ------------------------------------------------------------------------- */
@@ -343,7 +345,8 @@ FLAREPP_API int flarepp_mixer_backward_shared(int dtype, int64_t B, int64_t N, i
  * flarepp_mixer_forward_train computes O like flarepp_mixer_forward (on the
  * unfused kernels, the results agree within rounding) and leaves in `ws`
  * (flarepp_mixer_backward_workspace_bytes bytes) the projections K, V, K~,
- * V~, the decoded tokens Y, Q(X), Z and the three log-normalisers.
+ * V~, the decoded tokens Y, Q(X), Z, the three log-normalisers and (bf16) the
+ * weights re-laid out for the reverse pass.
  * flarepp_mixer_backward_from_saved then computes exactly what
  * flarepp_mixer_backward computes for the same inputs (bit for bit), given a
  * workspace that a flarepp_mixer_forward_train with the same sizes and inputs

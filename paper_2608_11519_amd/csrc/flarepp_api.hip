@@ -664,24 +664,27 @@ BwdWs bwd_ws(void* base, int dtype, int64_t B, int64_t N, int64_t C, int64_t H, 
   Carver cv(base);
   BwdWs w{};
   const bool gg = flarepp::grad_gemm_ok((int)C, (int)bs), rs = flarepp::rs_ok((int)D, (int)bs);
-  for (int i = 0; i < (dtype == FLAREPP_BF16 ? 5 : 4); ++i) w.wf[i] = cv.take(bs * C * C);
+  const MixerPlan pl = mixer_plan(dtype, B, N, C, H, M);
+  const bool fused = bwd_fused_encodes(dtype, pl), fdec = fused && bwd_fused_decode(T, C, D, Mp);
+  // W_O's: the training forward's merge, where no fused decode has one
+  for (int i = 0; i < 5; ++i) w.wf[i] = i < 4 || (dtype == FLAREPP_BF16 && !fdec) ? cv.take(bs * C * C) : nullptr;
   for (int i = 0; i < 5; ++i) w.wft[i] = (i < 4 ? gg : rs) ? cv.take(bs * C * C) : nullptr;
-  w.seeds_op = cv.take(bs * H * Mp * D);
+  w.seeds_op = fused ? nullptr : cv.take(bs * H * Mp * D);
   w.K = cv.take(bs * BH * N * D);
   w.Kt = cv.take(bs * BH * N * D);
   w.Vdm = cv.take(bs * BH * D * Np);
   w.Vtdm = cv.take(bs * BH * D * Np);
   w.Y = cv.take(bs * T * C);
-  w.q_op = cv.take(bs * BH * Mp * D);
-  w.z_op = cv.take(bs * BH * D * Mp);
+  w.q_op = fdec ? nullptr : cv.take(bs * BH * Mp * D);
+  w.z_op = fdec ? nullptr : cv.take(bs * BH * D * Mp);
   // the encodes' partials: the unfused route's chunks or the fused encode's
-  const MixerPlan pl = mixer_plan(dtype, B, N, C, H, M);
-  const bool fused = bwd_fused_encodes(dtype, pl);
   const int64_t Rp = std::max<int64_t>(e.nchunks, fused ? pl.nchunks : 1);
   if (fused) {
     w.fwf[0] = cv.take(bs * C * C);
     w.fwf[1] = cv.take(bs * C * C);
     w.fq_op = cv.take(bs * BH * Mp * D);
+  }
+  if (fdec) {
     w.fwo = cv.take(bs * C * C);
     w.fz_op = cv.take(bs * BH * flarepp::z_frag_elems_per_head((int)Mp, (int)D));
     w.fqnorm2 = (float*)cv.take(f4 * BH * (Mp / 4));
@@ -707,7 +710,9 @@ BwdWs bwd_ws(void* base, int dtype, int64_t B, int64_t N, int64_t C, int64_t H, 
   if (rs) {
     w.rs = flarepp::rs_split(B, H, N, (int)D, (int)Mp);
     w.dec.R = w.enc.R = w.rs.R;
-    w.lc = cv.take((size_t)16 * BH * N);
+    // read by call 3, before call 1 writes dV~ (2 B N C bytes, at least twice
+    // the 16 B H N of the row terms)
+    w.lc = w.dVt;
   } else {
     w.c1 = (float*)cv.take(f4 * BH * Mp);
     w.c2 = (float*)cv.take(f4 * BH * Mp);
@@ -728,7 +733,7 @@ BwdWs bwd_ws(void* base, int dtype, int64_t B, int64_t N, int64_t C, int64_t H, 
   const int64_t R = std::max<int64_t>(std::max(w.dec.R, w.enc.R), 1);
   w.pa = (float*)cv.take(f4 * BH * R * Mp * D);
   w.pg = (float*)cv.take(f4 * BH * R * Mp * D);
-  w.pq = (float*)cv.take(f4 * BH * R * Mp * D);
+  w.pq = w.pg;  // call 2 writes it after the sum of call 3's pg
   if (gg) {
     w.wg_prob = bwd_lo_parts(dtype) ? 7 : 5;
     w.splits = flarepp::wgrad_chunks(T, w.wg_prob, &w.wg_chunk);

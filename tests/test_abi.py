@@ -346,3 +346,15 @@ def test_noalloc_rejects_shapes_beyond_its_scratch_array_before_any_hip_call():
     assert rc == fp.ERR_UNSUPPORTED
     # invalid shapes as for the mixer
     assert lib.flarepp_mixer_forward_noalloc(fp.BF16, 1, 100, 100, 3, 32, *ptrs, None) == fp.ERR_INVALID_ARG
+
+
+@pytest.mark.parametrize("dt,C,H,M", [(fp.BF16, 128, 8, 512), (fp.BF16, 256, 8, 256), (fp.BF16, 64, 1, 64), (fp.F32, 64, 4, 100)])
+def test_backward_workspace_is_what_the_header_states(dt, C, H, M):
+    # 10 or 12 token arrays and the decode's normalisers; the rest does not
+    # grow with the tokens (one round of workgroups' partial sums)
+    _lib()
+    size = lambda N: fp.flarepp_mixer_backward_workspace_bytes(dt, 1, N, C, H, M)  # noqa: E731
+    token = (10 * 4 if dt == fp.F32 else 12 * 2) * C + 4 * H
+    a, b = 1 << 20, 1 << 21
+    assert size(b) - size(a) <= 1.001 * token * (b - a)
+    assert size(a) <= 1.05 * token * a
