@@ -295,8 +295,9 @@ FLAREPP_API int flarepp_mixer_forward_shared(int dtype, int64_t B, int64_t N, in
  * bf16 parts (hi + lo, ~16 bits), because the weight gradients X^T dV are
  * made of their small token-dependent part; accumulation is fp32.
  *
- * Sizes as for the mixer; in addition B*N <= 2^30 (FLAREPP_ERR_UNSUPPORTED
- * otherwise).  Workspace:
+ * Sizes as for the mixer; in addition B*N <= 2^30, and with fp32, or bf16 at
+ * D = 64, M up to 18,752 at the least (FLAREPP_ERR_UNSUPPORTED otherwise).
+ * Workspace:
  * flarepp_mixer_backward_workspace_bytes(...) bytes (0 for an invalid or
  * unsupported shape); it holds the forward's K, V, K~, V~, Y, the token
  * gradients dY, dK, dV, dK~, dV~ (and the low parts of dV, dV~ with bf16) and

@@ -749,6 +749,11 @@ BwdWs bwd_ws(void* base, int dtype, int64_t B, int64_t N, int64_t C, int64_t H, 
 int check_backward_shape(int dtype, int64_t B, int64_t N, int64_t C, int64_t H, int64_t M) {
   TRY(check_mixer_shape(dtype, B, N, C, H, M));
   if (B * N > (int64_t(1) << 30)) return fail(FLAREPP_ERR_UNSUPPORTED, "B*N too large for the backward");
+  // k_attn_bwd keeps two values of every route in LDS, beside one wave's window
+  const int bs = dtype_bytes(dtype);
+  const int64_t D = C / H;
+  if (!flarepp::rs_ok((int)D, bs) && !flarepp::attn_bwd_waves((int)D, 1, (int)round_up(M, 32), false, bs))
+    return fail(FLAREPP_ERR_UNSUPPORTED, "M=%lld is too large for the backward in this type and head width", (long long)M);
   return FLAREPP_OK;
 }
 

@@ -358,3 +358,15 @@ def test_backward_workspace_is_what_the_header_states(dt, C, H, M):
     a, b = 1 << 20, 1 << 21
     assert size(b) - size(a) <= 1.001 * token * (b - a)
     assert size(a) <= 1.05 * token * a
+
+
+@pytest.mark.parametrize("dt,C,H,most", [(fp.F32, 64, 4, 19616), (fp.F32, 64, 1, 18752), (fp.BF16, 128, 2, 19008)])
+def test_backward_refuses_routes_that_do_not_fit(dt, C, H, most):
+    # (a division by zero in the work split before)
+    _lib()
+    assert fp.flarepp_mixer_backward_workspace_bytes(dt, 1, 1000, C, H, most) > 0
+    for M in (most + 1, 65536):
+        assert fp.flarepp_mixer_backward_workspace_bytes(dt, 1, 1000, C, H, M) == 0
+        assert fp.flarepp_block_backward_workspace_bytes(dt, 1, 1000, C, H, M) == 0
+        assert "too large" in fp.last_error()
+    assert fp.flarepp_mixer_backward_workspace_bytes(fp.BF16, 1, 1000, 64, 4, 65536) > 0
