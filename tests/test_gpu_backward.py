@@ -77,10 +77,10 @@ def test_backward_tails_and_route_counts(N, M):
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_backward_several_tiles_per_wave_with_tail(dtype):
-    # two heads over 40,013 tokens: 1,251 position tiles per (b, h), so each
-    # wave of the SDPA backward walks two of them (in bf16 at D = 16 the
-    # second tile's rows are staged through LDS during the first), and the
-    # last tile holds 13 positions
+    # two heads over 40,013 tokens: 1,251 position tiles per (b, h), the last
+    # one of 13 positions; in fp32 each wave of the SDPA backward walks several
+    # of them, in bf16 at D = 16 a workgroup takes one step of 16 tiles (its
+    # later steps are test_gpu_backward_steps.py's)
     w = inp.Workload("bwd-tiles", 1, 40013, 32, 2, 40, dtype, "normal")
     _check(w, inp.make_inputs(w, 11, seed_scale=4.0), "tiles-tail")
 
