@@ -5,8 +5,8 @@
 // (32 routes each) and a chunk of the N positions.  Its waves form RW route
 // groups x PW = 8 / RW position groups; a wave keeps RB route blocks in
 // registers for the whole launch (operands, their gradient accumulators and,
-// in an encode, -L and -c as the initial accumulators of the score products)
-// and walks its position group's tiles of 32 positions.  The position-side
+// in an encode, -L and -c as operands of one more product, below) and walks its
+// position group's tiles of 32 positions.  The position-side
 // rows of the next step are copied into LDS while the current one runs.
 //
 // "Query" is the side whose softmax row it is (routes in an encode,
@@ -14,8 +14,9 @@
 //   S' = Q K^T - L,  dP' = dOut V^T - c          (rows = queries, cols = keys)
 //   P = 2^S',  dS = P dP'
 //   key side    dV^T += dOut^T P,  dK^T += Q^T dS  (P, dS as they lie)
-//   query side  dQ^T += K^T dS^T                   (dS transposed on the MFMA)
-// so a tile needs one transpose only.  D = 16 takes its gradient products on
+//   query side  dQ^T += K^T dS^T                   (dS transposed through LDS)
+// so a tile needs one transpose only (2 KiB of the wave's own, read back by
+// transposing LDS reads).  D = 16 takes its gradient products on
 // v_mfma_f32_16x16x32 (no rows wasted on a 32-row tile of 16 channels); two
 // v_permlane16_swap per register pair turn the 32 x 32 result into its two
 // 16-column operands.

@@ -466,7 +466,7 @@ __global__ __launch_bounds__(256, 1) void k_attn_bwd(AttnBwdParams p) {
     float Ll = 0.f, cl = 0.f;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) kb[ks] = long_frag(blo, p.blo_sn, p.blo_sd, nc, 16 * ks + 8 * g, nok);
-    if (D == 32 && p.glo_sn == 1) {  // wave-uniform (at D = 16 the staging would cost the second wave per SIMD)
+    if (D == 32 && p.glo_sn == 1) {  // wave-uniform (D = 16 and 64 take the element loads below)
       // d-major values (each head's rows padded to whole 32-position tiles):
       // the tile's D rows of 32 positions go through the wave's transpose
       // tile with 16-byte loads (chunk r: row r / 4, positions 8 (r % 4) ..

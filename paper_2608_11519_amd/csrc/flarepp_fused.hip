@@ -2256,8 +2256,10 @@ static hipError_t dec_launch(const DecFusedParams& pp, hipStream_t s) {
       k_decode_fused<T, D, KSC, W><<<wgrid, 64 * W, lds, s>>>(p);
       return hipGetLastError();
     };
-    // four waves wherever two such workgroups fit a CU's LDS (they were the
-    // faster form at every size measured, above)
+    // four waves wherever two such workgroups fit a CU's LDS: at D = 32 the
+    // faster form (above); at D = 16 and 64 the forward of 1,024 .. 160,000 tokens,
+    // M = 8 .. 224 and 8 .. 96, is 0 to 15% faster with it and never slower by
+    // more than a repetition differs (1%)
     const int pair = decode_pair_elems(16 * KSC, D, p.Mp);
     const size_t lds4 = ((D == 64 ? 2 : 1) * KSC * kFrag + 2 * (size_t)pair + (D == 16 ? 16 : 0)) * sizeof(T);
     if (lds4 <= 80 * 1024) {

@@ -13,7 +13,7 @@
 //   of the rows per workgroup, which read B twice).
 // * k_rows_sum, k_rows_sum_stream: dX = sum_j G_j W_j^T over the four
 //   projections by persistent workgroups.  2^20 x 128: 300 us for 1.6 GB (5.4
-//   TB/s; 413 us as a tiled GEMM); 100,000 x 256: 89 us (172).
+//   TB/s; 413 us as a tiled GEMM); 100,000 x 256: 87 us (172).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -258,11 +258,14 @@ __global__ __launch_bounds__(512) void k_rows_sum(RowsSumParams p) {
 // The same product at C = 256, where the four weights (512 KiB) do not fit in
 // LDS: the tokens' rows do the waiting there instead.  A workgroup walks tiles
 // of 64 tokens; each projection's rows [64][256] are one slot of a ring of
-// four (direct copies, up to three slots ahead), and a wave computes 32 output
+// four (direct copies, issued three slots ahead), and a wave computes 32 output
 // columns for all 64 tokens with its weight fragments read from L2, which
-// holds all four weights, one projection ahead.  Every row is read once
-// (100,000 tokens: 89 us for 307 MB; a quarter of the columns per workgroup with the
-// weights in LDS read them four times: 138 us).
+// holds all four weights, one projection ahead.  Those are ordinary loads, and
+// the compiler, which does not see the copies issued behind them, waits for
+// them down to zero at the next step's start: a step's copies have one step to
+// land, not three, and the counted wait ahead of the barrier only orders them.
+// Every row is read once (100,000 tokens: 87 us for 307 MB; a quarter of the columns
+// per workgroup with the weights in LDS read them four times: 138 us).
 __global__ __launch_bounds__(512) void k_rows_sum_stream(RowsSumParams p) {
   constexpr int C = 256, KS = 16, TOK = 64, SLOT = TOK * C * 2, RING = 4;
   __shared__ __attribute__((aligned(16))) char smem[RING * SLOT];

@@ -191,8 +191,6 @@ __device__ __forceinline__ void row_terms(const ProjParams& p, int b, int xrow, 
   }
 }
 
-template <typename T, int NQ>
-struct ProjExtra;
 template <typename T, int NQ = kProjBlocks, int LAYOUT = -1>
 __device__ __forceinline__ void proj_store(const ProjParams& p, int b, int n0, int w, int cg,
                                            const f32x16 (&acc)[NQ], const ProjExtra<T, NQ>* extra = nullptr);
@@ -953,8 +951,8 @@ hipError_t launch_layernorm_bwd(const LayerNormBwdParams& p, float* dgamma, floa
 
 template <typename T>
 hipError_t launch_project(const ProjParams& p, hipStream_t s) {
-  // the persistent form: bf16, C = 64 or 128, every weight in LDS, and one
-  // of its layout patterns
+  // the persistent form: bf16, C = 64 or 128 (every weight in LDS) or 256 (one
+  // weight per workgroup), and one of its layout patterns
   int pat = -1;
   {
     bool kv = (p.nw == 2 || p.nw == 4), tok = true;
