@@ -750,18 +750,18 @@ __global__ __launch_bounds__(64 * W) void k_encode_fused(EncFusedParams p) {
 // folded pairwise.  A slice reads whole rows of neighbouring lanes, and only 4
 // channels per lane are exchanged.  What bounds it is the chain of round
 // trips, in two forms:
-//  * few chunks (one batch of 8 per slice, 16 lanes per row): many rows, so
-//    the registers of small batches keep more waves in flight;
-//  * many chunks come with few rows (the encode's plan fills the CUs with
-//    one or the other): 64 partials of a row in flight at every D, by batches of
-//    16 and D lanes per row.
+//  * few chunks (batches of up to 8, 16 lanes per row) or many rows: the
+//    registers of small batches keep more waves in flight;
+//  * many chunks of few rows: 64 partials of a row in flight at every D, by
+//    batches of 16 and D lanes per row, while its workgroups fit two on a CU.
 // us, few / many form, by rocprof: 4 chunks of 16,384 rows 4.0 / 5.7 (D = 16),
 // 4.2 / 8.5 (32), 5.8 / 19.1 (64); 157 chunks of 128 rows 8.8 / 7.6, 14.3 / 7.7,
 // 25.8 / 7.6; 512 chunks 22 / 16, 39 / 17, 76 / 16.  With the loads behind the
 // tests of the maxima, where the compiler puts them, a batch takes two round
-// trips: 64 chunks of 128 rows 5.0 us (D = 16), now 4.6.
+// trips: 64 chunks of 128 rows 5.0 us (D = 16), now 4.6.  The line, at D = 64: 24
+// chunks of 2,048 rows 6.5 / 5.3, of 4,096 7.9 / 8.4; 12 of 4,096 6.2 / 7.3.
 // ---------------------------------------------------------------------------
-constexpr bool combine_many(int R, int D) { return R > 8 * (64 / D); }
+constexpr bool combine_many(int R, int D, int64_t rows) { return R > 8 * (64 / D) && rows * D <= 512 * 256; }
 
 template <typename T, int D, bool MANY>
 __global__ __launch_bounds__(256) void k_combine_par(CombineParams p) {
@@ -830,7 +830,7 @@ __global__ __launch_bounds__(256) void k_combine_par(CombineParams p) {
     } else if (p.R <= 4 * RG) {
       fold(std::integral_constant<int, 4>{}, rg);
     } else {
-      fold(std::integral_constant<int, 8>{}, rg);
+      for (int r0 = rg; r0 < p.R; r0 += 8 * RG) fold(std::integral_constant<int, 8>{}, r0);
     }
 #pragma unroll
     for (int k = DQ; k < LPR; k <<= 1) {
@@ -2158,7 +2158,7 @@ hipError_t launch_encode_fused(const EncFusedParams& p, int D, int waves, hipStr
 
 template <typename T, int D>
 static void combine_go(const CombineParams& p, hipStream_t s) {
-  const bool many = combine_many(p.R, D);
+  const bool many = combine_many(p.R, D, p.BH * p.Mp);
   // (a launch holds fewer than 2^32 threads)
   const unsigned grid = (unsigned)std::min<int64_t>(p.BH * (p.Mp / (many ? 256 / D : 16)), 1 << 23);
   if (many) k_combine_par<T, D, true><<<grid, 256, 0, s>>>(p);

@@ -75,6 +75,22 @@ def test_chunk_counts(monkeypatch, D, chunks):
     np.testing.assert_allclose(lse.cpu().numpy(), L, rtol=0, atol=1e-4)
 
 
+# more rows than two workgroups per CU hold: several batches of 8 per slice
+@pytest.mark.parametrize("D,B,chunks", [(16, 150, 33), (16, 150, 70), (32, 80, 17), (32, 80, 35), (64, 40, 9), (64, 40, 21)])
+def test_chunk_counts_of_many_rows(monkeypatch, D, B, chunks):
+    monkeypatch.setenv("FLAREPP_FORCE_CHUNKS", str(chunks))
+    H, M, N = 1, 90, 32 * chunks - 13
+    assert B * H * 96 * D > 512 * 256
+    q = inp.make_tensor((B, H, M, D), 56, "f32", scale=2.0)
+    k = inp.make_tensor((B, H, N, D), 57, "f32")
+    v = inp.make_tensor((B, H, N, D), 58, "f32")
+    out, lse = fp.flarepp_route(fp.ENCODE, *(torch.from_numpy(x).cuda() for x in (q, k, v)), want_lse=True)
+    torch.cuda.synchronize()
+    ref, L = orc.sdpa(q, k, v)
+    assert_close("out", out.cpu().numpy(), ref, TOL["f32"], f"D{D} R{chunks}")
+    np.testing.assert_allclose(lse.cpu().numpy(), L, rtol=0, atol=1e-4)
+
+
 @pytest.mark.parametrize("chunks", [1, 200])
 @pytest.mark.parametrize("row", [0, 1, 2, 3, 30])
 @pytest.mark.parametrize("D", [16, 32, 64])
