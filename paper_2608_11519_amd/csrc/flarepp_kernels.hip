@@ -962,7 +962,13 @@ hipError_t launch_project(const ProjParams& p, hipStream_t s) {
     }
     pat = kv ? kPatKV : tok ? kPatTok : (p.nw == 1 && p.layout[0] == kPlain) ? kPatPlain : -1;
   }
-  const bool one = p.C == 256;  // one weight per workgroup
+  // C = 256 copies 128 KiB of weights per workgroup first: it pays from about 1,024
+  // tiles x weights on, and where a wave has a SIMD to itself (four projections,
+  // general / persistent form in us with the weight fragments: 64 tokens 14.5 / 12.2,
+  // 256 14.1 / 17.0, 4,096 15.0 / 18.3, 8,192 19.7 / 20.0, 12,000 26.7 / 22.2; one
+  // projection: 20,000 16.8 / 19.6, 32,768 20.9 / 20.9, 50,000 32.3 / 21.7)
+  const int64_t tiles = (int64_t)p.B * (p.Np / 32);
+  const bool one = p.C == 256 && (tiles <= 4 || tiles * p.nw > 1024);  // one weight per workgroup
   const size_t lds = (size_t)(one ? 1 : p.nw) * p.C * p.C * sizeof(T);
   if (std::is_same<T, __bf16>::value && (p.C == 64 || p.C == 128 || one) && lds <= 160 * 1024 && pat >= 0) {
     using Kern = void (*)(ProjParams);
@@ -977,7 +983,6 @@ hipError_t launch_project(const ProjParams& p, hipStream_t s) {
     if (e == hipSuccess)
       e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
-    const int64_t tiles = (int64_t)p.B * (p.Np / 32);
     // one weight per workgroup: streams in multiples of 8 (one XCD each)
     const unsigned grid = one ? (unsigned)(std::min<int64_t>((blocks_for(tiles, 8) + 7) / 8 * 8, std::max(ncu / p.nw / 8 * 8, 8)) * p.nw)
                               : (unsigned)std::min<int64_t>(blocks_for(tiles, 8), std::max(ncu, 1));

@@ -109,3 +109,16 @@ def test_projection_several_tiles_wide():
     _, _, Kt1, _ = fp.flarepp_project(t["X"], Wkt=t["Wkt"], H=w.H)
     torch.cuda.synchronize()
     assert torch.equal(Kt1, outs[2])
+
+
+@pytest.mark.parametrize("N", [33, 128, 129, 8192, 8193])
+def test_projection_forms_wide(N):
+    # C = 256, four weights: the persistent form up to 4 tiles of 32 tokens and
+    # from 1,025 tiles x weights on, the general one between
+    w = inp.Workload("proj-forms", 1, N, 256, 16, 8, "bf16", "normal")
+    d = inp.make_inputs(w, 74)
+    t = upload(d, w)
+    outs = fp.flarepp_project(t["X"], t["Wk"], t["Wv"], t["Wkt"], t["Wvt"], H=w.H)
+    torch.cuda.synchronize()
+    for name, W, got in zip(("K", "V", "Kt", "Vt"), ("Wk", "Wv", "Wkt", "Wvt"), outs):
+        assert_close(name, got.float().cpu().numpy(), orc.project(d["X"], d[W], w.H), TOL["bf16"] / 2, f"project-{N}")
