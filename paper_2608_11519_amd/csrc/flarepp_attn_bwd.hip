@@ -30,17 +30,23 @@
 // position-side ones are summed over the RW route groups through LDS, in a
 // fixed order, one step later (so there is one barrier per step).
 //
-// What bounds it: a tile issues 58 vector instructions (16 of them
-// exponentials at half rate) and 9 or 10 MFMAs, about 350 clocks of the SIMD's
-// vector pipe, which is busy 0.6 of the time; the rest is the barrier of a
-// step (the older wave of a SIMD runs ahead and waits for the younger) and the
-// sum over the route groups.  At N = 2^20, C = 128, H = 8, M = 512: decode
-// 1.15 ms, encodes 1.22 and 1.26 ms (the second adds to a gradient), against
-// 3.29, 2.46 and 2.47 ms for the kernel that kept the positions in registers
-// and walked the routes (it read every route operand per tile, added into a
-// per-wave LDS slot per tile and needed two and four route windows there).
-// At 2 x 50,000 x 256, H = 8, M = 256 (D = 32): 116, 147 and 164 us against
-// 418, 255 and 277.
+// What bounds it at D = 16: the vector pipe and the waits around it.  By shader
+// counters at N = 2^20, M = 512, a tile of 32 positions times a route block costs
+// a wave of an encode 88 vector instructions (16 of them exponentials at half
+// rate, the sums over the route groups and the stores included), 458 clocks of
+// the pipe, and 10 MFMAs; of the decode 78, 410 and 8.75.  The pipe is busy 0.66
+// and 0.69 of the time, the matrix pipe 0.32 and 0.30; the rest is the barrier of
+// a step (the older wave of a SIMD runs ahead and waits for the younger), the
+// sum over the route groups and LDS bank conflicts (17 and 22 clocks).  At D = 32
+// (2 x 50,000 x 256, M = 256: one tile per barrier) the pipe is busy 0.4 of the
+// time and the waits are 0.3 to 0.4 of it.
+// At N = 2^20, C = 128, H = 8, M = 512: decode 1.10 ms, encodes 1.22 and 1.26 ms
+// (the second call's adds to a gradient, and its sums wait for the copies issued
+// just before), against 3.29, 2.46 and 2.47 ms for the kernel that kept the
+// positions in registers and walked the routes (it read every route operand per
+// tile, added into a per-wave LDS slot per tile and needed two and four route
+// windows there).  At 2 x 50,000 x 256, H = 8, M = 256 (D = 32): 116, 147 and 164 us
+// against 418, 255 and 277.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
